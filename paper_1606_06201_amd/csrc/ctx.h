@@ -6,6 +6,42 @@ namespace ipmg {
 
 struct Ctx;
 
+// Device memory of a context, given back when the context goes.  Buffers of less
+// than 1 MB are cut from slabs of 4 MB instead of being allocations of their own:
+// a small grid's kernels touch dozens of them, and each allocation is at least one
+// page of its own to translate.
+struct Arena {
+  static constexpr size_t SLAB = (size_t)4 << 20, SMALL = (size_t)1 << 20, ALIGN = 256;
+  std::vector<void*> blocks;
+  char* slab = nullptr;
+  size_t used = SLAB;
+  void* raw(size_t bytes) {
+    void* p = nullptr;
+    blocks.reserve(blocks.size() + 1);
+    if (hipMalloc(&p, bytes) != hipSuccess) throw Error(IPMG_E_NOMEM, "device allocation failed");
+    blocks.push_back(p);
+    return p;
+  }
+  void* alloc(size_t bytes) {
+    bytes = (bytes + ALIGN - 1) / ALIGN * ALIGN;
+    if (bytes == 0) bytes = ALIGN;
+    if (bytes >= SMALL) return raw(bytes);
+    if (used + bytes > SLAB) {
+      slab = (char*)raw(SLAB);
+      used = 0;
+    }
+    void* p = slab + used;
+    used += bytes;
+    return p;
+  }
+  void release() {
+    for (void* p : blocks) (void)hipFree(p);
+    blocks.clear();
+    slab = nullptr;
+    used = SLAB;
+  }
+};
+
 // Level arrays (precision of the V-cycle, T = float or double).
 struct Level {
   Dims d;
@@ -15,9 +51,27 @@ struct Level {
   void* t = nullptr;    // residual
   void* E = nullptr;    // coarse element matrices (NSYM * m), levels below the finest
   double* E64 = nullptr;// the same in FP64: the Galerkin chain is formed in FP64 (aliases E in FP64 mode)
+  void* S = nullptr;    // node stencil (stencil.h), and the reciprocal diagonal per slot
+  void* dinv = nullptr;
   void* bZ = nullptr;   // border vector of Z on this level (n_slots)
   double* bZ64 = nullptr;// the same in FP64 (aliases bZ in FP64 mode)
 };
+
+// Lambda entry of a level vector that its producer left as partials of b'v (see
+// LamRef in kernels.h): the fields of the reference without its type.
+struct LamPend {
+  int kind = 0;
+  const void* value = nullptr;
+  const void* r = nullptr;
+  const double* omg = nullptr;
+  const double* part = nullptr;
+  unsigned nb = 0;
+};
+
+// Passes of a level in node-stencil form (the kernels' StenMode).
+enum StenPass { SP_JACOBI2 = 0, SP_JACOBI = 1, SP_RESID = 2, SP_BETA = 3 };
+// Largest order of the coarsest solve inside the one-workgroup V-cycle (its threads).
+constexpr int TAIL_MAX_LD = 512;
 
 // Kernel set of one dimension (implemented for 2 and 3 in ops2d.hip / ops3d.hip).
 struct Ops {
@@ -59,6 +113,25 @@ struct Ops {
   virtual void galerkin(Ctx& c, int lev_f, int op) = 0;              // E64 of level lev_f-1
   virtual void dense_assemble(Ctx& c, int op, double* A, int n) = 0;
   virtual void power_start(Ctx& c, int lev, int aug, void* v) = 0;
+  // Levels in node-stencil form (stencil.h).
+  //   sten_level: the level's passes run on its stencil; tail_level: the highest
+  //   level of the one-workgroup V-cycle (0: none); needs_elements: the level's
+  //   passes read the element matrices in V-cycle precision.
+  virtual bool sten_level(const Ctx& c, int lev, int op) const = 0;
+  virtual int tail_level(const Ctx& c, int op) const = 0;
+  virtual bool needs_elements(const Ctx& c, int lev, int op) const = 0;
+  // Stencils and the damping of every level above.
+  virtual void sten_setup(Ctx& c, int op) = 0;
+  virtual void sten_damping(Ctx& c, int op, int steps, double product) = 0;
+  // One pass (StenMode) over lev from v (lambda entry in) to out; returns how out's
+  // lambda entry is found.  sten_jacobi0: the first sweep from zero alone.
+  virtual LamPend sten_pass(Ctx& c, int lev, int op, int mode, void* v, const void* r, void* out, const LamPend& in,
+                            const int* gate, const double* dot64) = 0;
+  virtual void sten_jacobi0(Ctx& c, int lev, int op, const void* r, void* out, const int* gate) = 0;
+  virtual bool sten_fuses_two(const Ctx& c, int lev, int op) const = 0;
+  virtual void lam_store(Ctx& c, const LamPend& p, void* out, const int* gate) = 0;
+  // V-cycle of levels 0..tail_level: lev.r -> lev.z of that level.
+  virtual void tail(Ctx& c, int op, const int* gate, const double* beta64) = 0;
   // Fused passes of level lev (see fused2d.h): false when they do not apply.
   //   down: lev.r -> z2 (into z), coarse residual (into lev-1 .r)
   //   up:   z2 (in z), coarse correction zc -> out
@@ -107,6 +180,7 @@ Ops* make_ops2d();
 Ops* make_ops3d();
 
 struct Ctx {
+  Arena arena;
   ipmg_desc desc{};
   int dim = 2;
   bool fp32 = true;
@@ -131,6 +205,13 @@ struct Ctx {
   bool fold_rn2_fin = true;          // PCG ||r||^2 finalize done by the V-cycle's first pass
   bool fold_restrict = true;         // finest residual restricted inside the first coarse down pass
   const void* down_from_t = nullptr; // ... the residual, pending for that pass
+  bool tail_on = true;         // small levels' V-cycle in one workgroup
+  bool step_in_tail = false;   // the tail ends the PCG step (finest level in the tail) ...
+  unsigned step_blocks = 0;    // ... whose direction kernel left this many blocks' partials
+  int step_first = 0;
+  LamPend lam_t, lam_z;        // lambda entries pending for the next restriction / prolongation
+  int sten_par = 0;            // partial buffer of the next stencil pass
+  double* pow_part = nullptr;  // partials of the batched damping estimate
   unsigned rn2_fin_blocks = 0;       // pending ||r||^2 finalize (partials of the update kernel) ...
   bool rn2_fin_zpend = false;        // ... and whether it marks z += alpha p pending
   bool fold_prolong = true;          // 2D tiled levels: prolongation folded into the first post-sweep, and
@@ -164,6 +245,7 @@ struct Ctx {
   double *dA = nullptr, *dLi = nullptr, *dAi = nullptr;   // packed tiles: A (then L), L^-1, A^-1
   float* dAif = nullptr;       // A^-1 rounded to FP32 (FP32 V-cycle)
   double* dpart = nullptr;     // partial sums of the dense apply
+  void* dfull = nullptr;       // A^-1 in full (V-cycle precision), for the one-workgroup V-cycle
 
   // per-level damping on the device: omega_dev[k] = weight, omega_dev[L + k] = rho estimate
   double* omega_dev = nullptr;
@@ -191,17 +273,12 @@ struct Ctx {
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   std::string err;
 
-  // 3D stored levels: element products y_e = E_e v of the level pass in flight
-  // (24 values per element of the largest stored level, V-cycle precision)
-  void* ye = nullptr;
-  bool elem_apply3 = true;
   // 3D finest level: element products of the pass's vector (V-cycle precision and
   // FP64, aliased in FP64 mode) and the set-up diagonal
   void* fine_ye = nullptr;
   double* fine_ye64 = nullptr;
   void* fine_dg = nullptr;
   bool elem_fine3 = true;
-  int64_t elem_apply3_min = 8192;   // ... on levels with at least this many elements
 
   // SIMP model: filtered densities and the penalised ones (m each)
   double* simp_xt = nullptr;

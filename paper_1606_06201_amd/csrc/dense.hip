@@ -292,9 +292,22 @@ __global__ __launch_bounds__(DTT) void k_dense_update(double* __restrict__ W, do
 
 // A^-1 = X' X: tile (I, J), I >= J, is sum_{K >= I} X_KI' X_KJ.  Blocks run in
 // row order, so the tiles with the longest sums start first.  With Af set, the
-// tile is also stored rounded to FP32 (the inverse an FP32 V-cycle applies).
+// tile is also stored rounded to FP32 (the inverse an FP32 V-cycle applies), with
+// full set into the full matrix that a one-workgroup V-cycle reads.
+template <typename T>
+__device__ inline void store_full(T* __restrict__ F, int ld, int I, int J, const double (&acc)[4][4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t r = I * DT + acc_row(i), c = J * DT + acc_col(j);
+      F[r * ld + c] = T(acc[i][j]);
+      if (I != J) F[c * ld + r] = T(acc[i][j]);
+    }
+}
 __global__ __launch_bounds__(DTT) void k_dense_product(const double* __restrict__ X, double* __restrict__ Ai,
-                                                       float* __restrict__ Af, int nt) {
+                                                       float* __restrict__ Af, int nt, void* __restrict__ full,
+                                                       int full_fp32) {
   __shared__ Tile SA, SB;
   int I, J;
   tri_index((int)blockIdx.x, I, J);
@@ -313,6 +326,10 @@ __global__ __launch_bounds__(DTT) void k_dense_product(const double* __restrict_
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) Af[dense_tile_off(I, J) + acc_row(i) * DT + acc_col(j)] = (float)acc[i][j];
+  }
+  if (full) {
+    if (full_fp32) store_full(static_cast<float*>(full), nt * DT, I, J, acc);
+    else store_full(static_cast<double*>(full), nt * DT, I, J, acc);
   }
 }
 
@@ -422,7 +439,8 @@ void dense_init(hipStream_t st, double* A, int n, int pad) {
   k_dense_init<<<nt * (nt + 1) / 2, DTT, 0, st>>>(A, n, pad);
 }
 
-void dense_factor_inverse(hipStream_t st, double* W, double* X, double* Ai, int n, const Red& red, float* Af) {
+void dense_factor_inverse(hipStream_t st, double* W, double* X, double* Ai, int n, const Red& red, float* Af,
+                          void* full, int full_fp32) {
   const int nt = dense_tiles(n);
   k_dense_init<<<nt * (nt + 1) / 2, DTT, 0, st>>>(X, n, 0);
   k_dense_diag<<<1, DTT, 0, st>>>(W, X, 0, red);
@@ -432,7 +450,7 @@ void dense_factor_inverse(hipStream_t st, double* W, double* X, double* Ai, int 
     const int nu = m * (m + 1) / 2 + m * (k + 1);
     if (nu > 0) k_dense_update<<<nu, DTT, 0, st>>>(W, X, k, nt, red);
   }
-  k_dense_product<<<nt * (nt + 1) / 2, DTT, 0, st>>>(X, Ai, Af, nt);
+  k_dense_product<<<nt * (nt + 1) / 2, DTT, 0, st>>>(X, Ai, Af, nt, full, full_fp32);
 }
 
 template <typename T, typename M>

@@ -328,16 +328,12 @@ struct OpFineZ {
 };
 
 // Coarse level: general symmetric element matrices from the Galerkin products,
-// packed upper-triangular, stored E[sym(r,c) * m + e].
-// ye (3D): the element products y_e = E_e v_e of the pass's vector, formed
-// beforehand by k_elem_apply3 (component-major, ye[r * m + e]); the node passes
-// then read three values per element instead of its 72 matrix entries and 24
-// nodal values.
+// packed upper-triangular, stored E[sym(r,c) * m + e].  (In 3D only its entries are
+// read: the level passes run on the assembled stencil, stencil.h.)
 template <int DIM, typename T>
 struct OpCoarse {
   const T* E;
   int64_t m;
-  const T* ye = nullptr;
   // Entry k of every element starts at the uniform address E + k m, so a load is
   // that base plus the element's 32-bit offset (no per-load 64-bit arithmetic).
   __device__ inline void rows(int64_t e, int, int, int, int a, const T* ve, T* acc) const {
@@ -788,57 +784,6 @@ __device__ inline void node_apply_fine3(const Op& op, const Dims& d, int i, int 
   }
 }
 
-// Element products of a stored 3D level, y_e = E_e v_e.  A block of 8 waves takes
-// 64 consecutive elements; wave a forms the three rows of local node a for all of
-// them (every matrix load coalesced over 64 elements, 72 entries and the 24 nodal
-// values per thread).  Nodal values of clamped nodes are read at node 0 (zero).
-constexpr int EA3_THREADS = 512;
-template <typename T>
-__global__ __launch_bounds__(EA3_THREADS) void k_elem_apply3(Dims d, const T* __restrict__ E,
-                                                             const T* __restrict__ v, T* __restrict__ ye,
-                                                             const int* gate) {
-  if (gate && *gate) return;
-  const int64_t e = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
-  const int a = threadIdx.x >> 6;
-  if (e >= d.m) return;
-  const int ei = (int)(e % d.nx), ej = (int)((e / d.nx) % d.ny), ek = (int)(e / ((int64_t)d.nx * d.ny));
-  T ve[24];
-#pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    const int ni = ei + loc_x(b), nj = ej + loc_y(b), nk = ek + loc_z(b);
-    const int64_t qn = ni >= 1 ? ((int64_t)nk * d.ny1 + nj) * d.nx1 + ni : 0;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) ve[b * 3 + c] = v[3 * qn + c];
-  }
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const int r = a * 3 + c;
-    T y = T(0);
-#pragma unroll
-    for (int col = 0; col < 24; ++col) y += E[sym_index(r, col, 24) * d.m + e] * ve[col];
-    ye[r * d.m + e] = y;
-  }
-}
-
-// Node rows and diagonal of a stored 3D level from the element products ye.
-template <typename T, bool ROWS, bool DIAG>
-__device__ inline void node_apply_ye3(const OpCoarse<3, T>& op, const Dims& d, int i, int j, int k, T* acc, T* dg) {
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int ex = q & 1, ey = (q >> 1) & 1, ez = q >> 2;
-    int ei = i - 1 + ex, ej = j - 1 + ey, ek = k - 1 + ez;
-    const bool ok = ei >= 0 && ei < d.nx && ej >= 0 && ej < d.ny && ek >= 0 && ek < d.nz;
-    const int64_t e = ok ? ((int64_t)ek * d.ny + ej) * d.nx + ei : 0;
-    const int a = loc_index(1 - ex, 1 - ey, 1 - ez);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const int r = a * 3 + c;
-      if constexpr (ROWS) acc[c] += ok ? op.ye[r * op.m + e] : T(0);
-      if constexpr (DIAG) dg[c] += ok ? op.E[sym_index(r, r, 24) * op.m + e] : T(0);
-    }
-  }
-}
-
 // Element products of the finest 3D level, y_e = x_e K0 v_e (+ h_e (h_e'v_e) for the
 // augmented system), one thread per element: all 24 rows, every matrix entry a
 // signed copy of one of the 14 cube constants at compile time (no matrix loads),
@@ -911,9 +856,6 @@ __device__ inline void node_apply_gather3(const Op& op, const Dims& d, int i, in
   if constexpr (fine3_op<Op>::value) {
     if ((!ROWS || op.ye) && (!DIAG || op.dgn))
       return node_apply_fine_ye3<T, ROWS, DIAG>(op.ye, op.dgn, op.m, d, i, j, k, acc, dg);
-  }
-  if constexpr (std::is_same<Op, OpCoarse<3, T>>::value) {
-    if (!ROWS || op.ye) return node_apply_ye3<T, ROWS, DIAG>(op, d, i, j, k, acc, dg);
   }
   if constexpr (std::is_same<Op, OpFineK<3, T>>::value) {
     return node_apply_fine3<T, Op, ROWS, DIAG>(op, d, i, j, k, v, acc, dg);
@@ -2250,21 +2192,78 @@ __global__ __launch_bounds__(BS) void k_dir_fin(const TY* __restrict__ y, const 
   }
 }
 
+// ------------------------------------------------------------ lambda entries --
+// Lambda entry of the vector a pass of the augmented system reads.  A sweep's own
+// lambda row needs b'v over the whole level; instead of a one-block kernel after
+// each sweep, the sweep stores its blocks' partials of b'v and whatever reads the
+// result next adds them itself (every block of the next pass, or one block of a
+// transfer), in one fixed order.  At 21 x 13 x 9 to 65 x 33 x 33 nodes the finalize
+// launch cost as much as the pass it followed.
+enum LamKind {
+  LAM_NONE = 0,
+  LAM_VALUE = 1,      // stored in the vector's last entry
+  LAM_SWEEP = 2,      // lp + omega (r - (b'v + c lp)) / c, lp the stored entry of the previous iterate
+  LAM_SWEEP2 = 3,     // the same with lp = omega r / c (previous iterate: the first sweep from zero)
+  LAM_RESID = 4       // r - (b'v + c lp): a residual's entry, lp the stored entry of v
+};
+template <typename T>
+struct LamRef {
+  int kind = LAM_NONE;
+  const T* value = nullptr;     // LAM_VALUE: the entry; LAM_SWEEP, LAM_RESID: the previous iterate's
+  const T* r = nullptr;         // lambda entry of the level's right-hand side
+  const double* omg = nullptr;  // damping of that level
+  double c = 0.0;
+  const double* part = nullptr; // partials of b'v of the previous iterate
+  unsigned nb = 0;
+};
+template <typename T>
+__device__ inline T lam_value(const LamRef<T>& L, double tot) {
+  if (L.kind == LAM_NONE) return T(0);
+  if (L.kind == LAM_VALUE) return *L.value;
+  const double r = (double)*L.r;
+  if (L.kind == LAM_RESID) return T(r - (tot + L.c * (double)*L.value));
+  const double w = *L.omg;
+  const double lp = L.kind == LAM_SWEEP ? (double)*L.value : (double)T(w * r / L.c);
+  return T(lp + w * (r - (tot + L.c * lp)) / L.c);
+}
+template <typename T>
+__device__ inline double lam_partials(const LamRef<T>& L, unsigned tid, unsigned nt) {
+  double s = 0.0;
+  for (unsigned b = tid; b < L.nb; b += nt) s += L.part[b];
+  return s;
+}
+// ... called by all NT threads of a block: the entry, in every thread.
+template <typename T, int NT>
+__device__ inline T lam_block(const LamRef<T>& L) {
+  __shared__ double sh[NT / 64];
+  const double s = wave_sum(lam_partials(L, threadIdx.x, NT));
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+  __syncthreads();
+  double tot = 0.0;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) tot += sh[w];
+  return lam_value(L, tot);
+}
+
 // ---------------------------------------------------------------- transfers --
 // 1D linear interpolation weight between a fine offset and its coarse node.
 __device__ inline float w1(int off) { return off == 0 ? 1.0f : 0.5f; }
 
 // Restriction rc = P' rf (transpose of the bilinear / trilinear prolongation,
-// Sec. 7), one thread per coarse node; clamped coarse nodes get 0.
+// Sec. 7), one thread per coarse node; clamped coarse nodes get 0.  lam: the lambda
+// entry of rf where its producer left partials (the first tile's block adds them).
 template <int DIM, typename T, typename TS = T>
 __global__ __launch_bounds__(BS) void k_restrict(Dims f, Dims c, const TS* __restrict__ rf,
-                                                 T* __restrict__ rc, int aug, const int* gate) {
+                                                 T* __restrict__ rc, int aug, LamRef<T> lam, const int* gate) {
   if (gate && *gate) return;
   const Tile tl = xcd_tile();
   const int I = tl.x * 64 + (threadIdx.x & 63);
   const int J = tl.y * (BS / 64) + (threadIdx.x >> 6);
   const int K = tl.z;
-  if (aug && I == 0 && J == 0 && K == 0) rc[c.nslots] = T(rf[f.nslots]);
+  if (aug && tl.x == 0 && tl.y == 0 && tl.z == 0) {
+    const T l = lam.kind != LAM_NONE ? lam_block<T, BS>(lam) : T(rf[f.nslots]);
+    if (threadIdx.x == 0) rc[c.nslots] = l;
+  }
   if (I >= c.nx1 || J >= c.ny1) return;
   const int64_t qc = ((int64_t)K * c.ny1 + J) * c.nx1 + I;
   T acc[DIM];
@@ -2292,16 +2291,19 @@ __global__ __launch_bounds__(BS) void k_restrict(Dims f, Dims c, const TS* __res
 }
 
 // Prolongation and correction z += P zc (Sec. 5.1 solution update), one thread
-// per fine node.
+// per fine node.  lam: the lambda entry of zc, as in k_restrict.
 template <int DIM, typename T>
-__global__ __launch_bounds__(BS) void k_prolong(Dims f, Dims c, T* __restrict__ z,
-                                                const T* __restrict__ zc, int aug, const int* gate) {
+__global__ __launch_bounds__(BS) void k_prolong(Dims f, Dims c, T* __restrict__ z, const T* __restrict__ zc, int aug,
+                                                LamRef<T> lam, const int* gate) {
   if (gate && *gate) return;
   const Tile tl = xcd_tile();
   const int i = tl.x * 64 + (threadIdx.x & 63);
   const int j = tl.y * (BS / 64) + (threadIdx.x >> 6);
   const int k = tl.z;
-  if (aug && i == 0 && j == 0 && k == 0) z[f.nslots] += zc[c.nslots];
+  if (aug && tl.x == 0 && tl.y == 0 && tl.z == 0) {
+    const T l = lam.kind != LAM_NONE ? lam_block<T, BS>(lam) : zc[c.nslots];
+    if (threadIdx.x == 0) z[f.nslots] += l;
+  }
   if (i >= f.nx1 || j >= f.ny1 || i == 0) return;
   const int64_t q = ((int64_t)k * f.ny1 + j) * f.nx1 + i;
   T acc[DIM];

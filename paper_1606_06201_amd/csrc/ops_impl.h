@@ -9,6 +9,8 @@
 #include "ctx.h"
 #include "kernels.h"
 #include "fused2d.h"
+#include "stencil.h"
+#include "dense.h"
 
 namespace ipmg {
 
@@ -1039,15 +1041,8 @@ struct OpsImpl : Ops {
     } else if (DIM == 2 && op == IPMG_OP_K && lev == c.L - 2 && c.coarse_from_x) {
       launch_level<T>(c, d, OpCoarse2K<DIM, T>{(const T*)c.xT, c.fine().nx, c.fine().m}, mode, (const T*)v, (const T*)r,
                       (T*)out, omg, aug, sidx, sidx_in, gate, dot64);
-    } else {
+    } else if constexpr (DIM == 2) {
       OpCoarse<DIM, T> o{(const T*)c.lev[lev].E, d.m};
-      // element products first (levels of 8192 elements and more: below, the
-      // extra launch costs more than the gathers it saves)
-      if (DIM == 3 && c.ye && mode != M_JACOBI0 && v && d.m >= c.elem_apply3_min) {
-        k_elem_apply3<T><<<(unsigned)((d.m + 63) / 64), EA3_THREADS, 0, c.stream>>>(d, o.E, (const T*)v,
-                                                                                     (T*)c.ye, gate);
-        o.ye = (const T*)c.ye;
-      }
       launch_level<T>(c, d, o, mode, (const T*)v, (const T*)r, (T*)out, omg, aug, sidx, sidx_in, gate, dot64);
     }
   }
@@ -1101,6 +1096,11 @@ struct OpsImpl : Ops {
     } else {
       ProfScope ps(c, PC_DIR_APPLY);
       k_dir_apply<DIM, TY, Op><<<g, BS, 0, c.stream>>>(op, d, y, pold, p, q, aug, c.red, first, gate);
+    }
+    if (c.step_in_tail) {                     // the tail adds the partials
+      c.step_blocks = g.x * g.y * g.z;
+      c.step_first = first;
+      return;
     }
     k_dir_fin<TY><<<1, BS, 0, c.stream>>>(y, pold, p, q, aug.b != nullptr, aug.c, d.nslots, first, c.red,
                                           g.x * g.y * g.z, gate, nullptr);
@@ -1157,26 +1157,321 @@ struct OpsImpl : Ops {
           (T*)c.fine_dg);
   }
 
+  // ------------------------------------------------------------- node stencils --
+  template <typename T>
+  static LamRef<T> lam_ref(const Ctx& c, const LamPend& p) {
+    LamRef<T> l;
+    l.kind = p.kind;
+    l.value = (const T*)p.value;
+    l.r = (const T*)p.r;
+    l.omg = p.omg;
+    l.c = c.cZ;
+    l.part = p.part;
+    l.nb = p.nb;
+    return l;
+  }
+  static unsigned sten_tiles(const Dims& d) { return (unsigned)((d.nnodes + 63) / 64); }
+  template <typename T>
+  static StenLevel<T> sten_of(const Level& l) {
+    return StenLevel<T>{(const T*)l.S, (const T*)l.dinv, (int)l.d.nnodes, l.d.nx1, l.d.nx1 * l.d.ny1};
+  }
+  // The one-workgroup tail takes the levels from the bottom up while their stencils
+  // stay below TAIL_BYTES each (one workgroup reads about 130 GB/s from L2: 640 KB
+  // is 5 us a pass, what a launch costs) and their vectors fit in its LDS; the
+  // finest level only below the register-blocked sizes.
+  static constexpr int64_t TAIL_BYTES = 320 * 1024;
+  // LDS entries of a level's vectors: r, pad, a, pad, b, pad (level 0: r, z, pad); a
+  // pad holds the neighbours that an index past either end of the grid can reach.
+  static int64_t tail_pad(const Dims& d) {
+    return DIM * ((DIM == 3 ? (int64_t)d.nx1 * d.ny1 : 0) + d.nx1 + 1);
+  }
+  static int64_t tail_lds(const Dims& d, bool coarsest) {
+    return coarsest ? 2 * d.nslots + tail_pad(d) : 3 * (d.nslots + tail_pad(d));
+  }
+  int tail_level(const Ctx& c, int op) const override {
+    if (!c.tail_on || c.L < 2) return 0;
+    int64_t lds = tail_lds(c.lev[0].d, true) * (int64_t)c.tsz;
+    int top = 0;
+    for (int k = 1; k < c.L && k < TAIL_LEVELS; ++k) {
+      const Dims& d = c.lev[k].d;
+      lds += tail_lds(d, false) * (int64_t)c.tsz;
+      if (sten_size<DIM>(d) * (int64_t)c.tsz > TAIL_BYTES || lds > TAIL_LDS) break;
+      if (k == c.L - 1 && DIM == 2 && d.nnodes >= c.tiled_min_nodes) break;
+      top = k;
+    }
+    return top;
+  }
+  bool sten_level(const Ctx& c, int lev, int op) const override {
+    if (lev < 1) return false;
+    if (lev <= tail_level(c, op)) return true;
+    if (DIM == 3) return lev < c.L - 1;
+    return op == IPMG_OP_Z && c.lev[lev].d.nnodes < c.tiled_min_nodes;
+  }
+  bool needs_elements(const Ctx& c, int lev, int op) const override {
+    return DIM == 2 && lev >= 1 && lev < c.L - 1 && !sten_level(c, lev, op);
+  }
+  // A^-1 of the coarsest level inside the tail: up to 200 KB (1.5 us of one
+  // workgroup's L2 reads; the two launches of the dense apply cost about 8 us).
+  bool tail_dense(const Ctx& c, int op) const {
+    const int64_t n = c.lev[0].d.nslots + (op == IPMG_OP_Z ? 1 : 0), ld = (int64_t)dense_tiles((int)n) * DT;
+    return n * ld * (int64_t)c.tsz <= 200 * 1024 && ld <= (c.fp32 ? TailNT<float>::value : TailNT<double>::value) / 2;
+  }
+  // Blocks whose partials every block of the next pass may add itself (16 KB);
+  // above, one block adds them in a launch of its own.
+  static constexpr unsigned LAM_FOLD_MAX = 2048;
+
+  template <typename T>
+  void sten_setup_t(Ctx& c, int op) {
+    for (int k = 1; k < c.L; ++k) {
+      if (!sten_level(c, k, op)) continue;
+      Level& l = c.lev[k];
+      const Dims& d = l.d;
+      if (!l.S) {
+        l.S = c.arena.alloc(sizeof(T) * (size_t)sten_size<DIM>(d));
+        l.dinv = c.arena.alloc(sizeof(T) * (size_t)d.nslots);
+      }
+      const unsigned g = sten_tiles(d);
+      T* S = (T*)l.S;
+      T* di = (T*)l.dinv;
+      if (k < c.L - 1)
+        k_sten_assemble<DIM, T, OpCoarse<DIM, double>>
+            <<<g, 64 * DIM, 0, c.stream>>>(OpCoarse<DIM, double>{l.E64, d.m}, d, S, di);
+      else if (op == IPMG_OP_K)
+        k_sten_assemble<DIM, T, OpFineK<DIM, double>>
+            <<<g, 64 * DIM, 0, c.stream>>>(OpFineK<DIM, double>{c.x64, d.m}, d, S, di);
+      else
+        k_sten_assemble<DIM, T, OpFineZ<DIM, double>>
+            <<<g, 64 * DIM, 0, c.stream>>>(OpFineZ<DIM, double>{c.x64, c.h64, d.m}, d, S, di);
+    }
+  }
+  void sten_setup(Ctx& c, int op) override {
+    if (c.fp32) sten_setup_t<float>(c, op);
+    else sten_setup_t<double>(c, op);
+  }
+
+  template <typename T>
+  TailArgs<T> tail_args(Ctx& c, int op) {
+    TailArgs<T> A{};
+    A.top = tail_level(c, op);
+    A.nu_pre = c.desc.nu_pre;
+    A.nu_post = c.desc.nu_post;
+    A.aug = op == IPMG_OP_Z;
+    A.cz = A.aug ? c.cZ : 1.0;
+    A.icz = 1.0 / A.cz;
+    int64_t off = 0;
+    for (int k = 0; k <= A.top; ++k) {
+      const Level& l = c.lev[k];
+      TailLevel<T>& t = A.lv[k];
+      t.L = sten_of<T>(l);
+      t.border = (const T*)(A.aug ? l.bZ : l.dinv);
+      t.r = (T*)l.r;
+      t.z = (T*)l.z;
+      t.nslots = (int)l.d.nslots;
+      t.ny1 = l.d.ny1;
+      t.nz1 = l.d.nz1;
+      t.rx = 1.0f / (float)l.d.nx1;
+      t.ry = 1.0f / (float)l.d.ny1;
+      t.pad = (int)tail_pad(l.d);
+      t.r_off = (int)off;
+      t.a_off = t.r_off + t.nslots + (k > 0 ? t.pad : 0);
+      t.b_off = k > 0 ? t.a_off + t.nslots + t.pad : 0;
+      off += tail_lds(l.d, k == 0);
+    }
+    A.omega = c.omega_dev;
+    IPMG_REQUIRE(off * (int64_t)sizeof(T) <= TAIL_LDS, IPMG_E_STATE, "one-workgroup levels exceed their LDS");
+    // the PCG residual in FP64 behind them, where it fits
+    const int64_t o64 = (off * (int64_t)sizeof(T) + 15) / 16 * 2;
+    A.r64_off = 8 * (o64 + c.lev[A.top].d.nslots) <= TAIL_LDS ? (int)o64 : -1;
+    return A;
+  }
+  template <typename T>
+  void tail_t(Ctx& c, int op, const int* gate, const double* beta64) {
+    constexpr int NT = TailNT<T>::value;
+    TailArgs<T> A = tail_args<T>(c, op);
+    if (c.step_blocks) {                      // ends the PCG step whose direction was formed last
+      A.pcg.nblk = c.step_blocks;
+      A.pcg.first = c.step_first;
+      A.pcg.pold = c.pp2;
+      A.pcg.p = c.pp;
+      A.pcg.q = c.pq;
+      A.pcg.z = c.pu;
+      A.pcg.r = c.pr;
+      c.step_blocks = 0;
+    }
+    const int n0 = (int)c.lev[0].d.nslots + A.aug;
+    if (tail_dense(c, op)) {
+      A.ainv = (const T*)c.dfull;
+      A.n0 = n0;
+      A.ld = dense_tiles(n0) * DT;
+      A.down = A.up = 1;
+      A.dot64 = beta64;
+      A.hflags = beta64 ? c.take_flag_dst() : nullptr;
+      k_tail<DIM, T><<<1, NT, 0, c.stream>>>(A, c.red, gate);
+      return;
+    }
+    A.down = 1;
+    k_tail<DIM, T><<<1, NT, 0, c.stream>>>(A, c.red, gate);
+    if constexpr (sizeof(T) == 4) dense_apply<float, float>(c.stream, c.dAif, c.dpart, n0, (const T*)c.lev[0].r, (T*)c.lev[0].z, gate);
+    else dense_apply<double, double>(c.stream, c.dAi, c.dpart, n0, (const T*)c.lev[0].r, (T*)c.lev[0].z, gate);
+    A.down = 0;
+    A.up = 1;
+    A.pcg.nblk = 0;
+    A.dot64 = beta64;
+    A.hflags = beta64 ? c.take_flag_dst() : nullptr;
+    k_tail<DIM, T><<<1, NT, 0, c.stream>>>(A, c.red, gate);
+  }
+  void tail(Ctx& c, int op, const int* gate, const double* beta64) override {
+    if (c.fp32) tail_t<float>(c, op, gate, beta64);
+    else tail_t<double>(c, op, gate, beta64);
+  }
+
+  template <typename T>
+  void sten_damping_t(Ctx& c, int op, int steps, double product) {
+    const int top = tail_level(c, op), aug = op == IPMG_OP_Z;
+    if (top > 0)
+      k_tail_power<DIM, T><<<(unsigned)top, TailNT<T>::value, 0, c.stream>>>(
+          tail_args<T>(c, op), steps, c.desc.omega, product, c.omega_dev, c.omega_dev + c.L);
+    PowArgs<T> A{};
+    unsigned nblk = 0;
+    for (int k = top + 1; k < c.L; ++k) {
+      if (!sten_level(c, k, op)) continue;
+      Level& l = c.lev[k];
+      IPMG_REQUIRE(A.nlev < POW_LEVELS, IPMG_E_STATE, "too many levels in the damping estimate");
+      PowLevel<T>& p = A.lv[A.nlev++];
+      p.L = sten_of<T>(l);
+      p.border = aug ? (const T*)l.bZ : nullptr;
+      p.v[0] = (T*)l.z;
+      p.v[1] = (T*)l.z2;
+      p.w = c.omega_dev + k;
+      p.rho = c.omega_dev + c.L + k;
+      p.nslots = (int)l.d.nslots;
+      p.ny1 = l.d.ny1;
+      p.blk0 = nblk;
+      p.nblk = sten_tiles(l.d);
+      nblk += p.nblk;
+    }
+    if (A.nlev == 0) return;
+    if (!c.pow_part) {   // room for every level that can be in the batch
+      size_t tiles = 0;
+      for (int k = 1; k < c.L; ++k) tiles += sten_tiles(c.lev[k].d);
+      c.pow_part = (double*)c.arena.alloc(sizeof(double) * (6 * tiles + 4 * (size_t)c.L));
+    }
+    double* part = c.pow_part;
+    for (int l = 0; l < A.nlev; ++l) {
+      A.lv[l].part = part;
+      A.lv[l].st = part + 6 * (size_t)A.lv[l].nblk;
+      part += 6 * (size_t)A.lv[l].nblk + 4;
+    }
+    for (int s = 0; s <= steps; ++s)
+      k_sten_power<DIM, T><<<nblk, 64 * Sten<DIM>::WAVES, 0, c.stream>>>(A, s, steps, aug, c.cZ);
+    k_sten_power_fin<T><<<(unsigned)A.nlev, BS, 0, c.stream>>>(A, steps, aug, c.cZ, c.desc.omega, product);
+  }
+  void sten_damping(Ctx& c, int op, int steps, double product) override {
+    if (c.fp32) sten_damping_t<float>(c, op, steps, product);
+    else sten_damping_t<double>(c, op, steps, product);
+  }
+
+  // Two sweeps from zero in one pass: always for K; for Z where the next pass adds
+  // the partials (the lambda entry of the result is never a launch of its own).
+  bool sten_fuses_two(const Ctx& c, int lev, int op) const override {
+    return op != IPMG_OP_Z || sten_tiles(c.lev[lev].d) <= LAM_FOLD_MAX;
+  }
+  template <typename T>
+  LamPend sten_pass_t(Ctx& c, int lev, int op, int mode, T* v, const T* r, T* out, const LamPend& in,
+                      const int* gate, const double* dot64) {
+    const Level& l = c.lev[lev];
+    const Dims& d = l.d;
+    const int aug = op == IPMG_OP_Z;
+    const unsigned g = sten_tiles(d);
+    IPMG_REQUIRE(g <= (unsigned)MAX_PARTIALS, IPMG_E_INVALID, "grid too large for one reduction");
+    const T* b = aug ? (const T*)l.bZ : nullptr;
+    const double* omg = c.omega_dev + lev;
+    LamRef<T> lam = lam_ref<T>(c, in);
+    T* lam_out = aug && (in.kind == LAM_SWEEP || in.kind == LAM_SWEEP2) ? v + d.nslots : nullptr;
+    if (aug) {
+      lam.r = r + d.nslots;
+      lam.omg = omg;
+    }
+    Red red = c.red;
+    red.partials += (size_t)c.sten_par * 4 * MAX_PARTIALS;
+    c.sten_par ^= 1;
+    double* part = aug || mode == ST_BETA ? red.partials : nullptr;
+    const StenLevel<T> L = sten_of<T>(l);
+    const unsigned nt = 64 * Sten<DIM>::WAVES;
+    {
+      ProfScope ps(c, c.prof_tag);
+      switch (mode) {
+        case ST_JACOBI2: k_sten<DIM, T, ST_JACOBI2><<<g, nt, 0, c.stream>>>(L, v, r, out, omg, b, lam, lam_out, dot64, part, gate); break;
+        case ST_JACOBI: k_sten<DIM, T, ST_JACOBI><<<g, nt, 0, c.stream>>>(L, v, r, out, omg, b, lam, lam_out, dot64, part, gate); break;
+        case ST_RESID: k_sten<DIM, T, ST_RESID><<<g, nt, 0, c.stream>>>(L, v, r, out, omg, b, lam, lam_out, dot64, part, gate); break;
+        default: k_sten<DIM, T, ST_BETA><<<g, nt, 0, c.stream>>>(L, v, r, out, omg, b, lam, lam_out, dot64, part, gate); break;
+      }
+    }
+    if (mode == ST_BETA) {
+      k_level_fin<T, M_JACOBI_BETA><<<1, BS, 0, c.stream>>>(v, r, out, omg, aug, c.cZ, d.nslots, dot64, red, g, 0, -1,
+                                                           gate, c.take_flag_dst());
+      return aug ? LamPend{LAM_VALUE, out + d.nslots} : LamPend{};
+    }
+    if (!aug) return LamPend{};
+    LamPend p;
+    p.kind = mode == ST_RESID ? LAM_RESID : (mode == ST_JACOBI2 ? LAM_SWEEP2 : LAM_SWEEP);
+    p.value = mode == ST_JACOBI2 ? nullptr : v + d.nslots;
+    p.r = r + d.nslots;
+    p.omg = omg;
+    p.part = red.partials;
+    p.nb = g;
+    if (g <= LAM_FOLD_MAX) return p;
+    lam_store(c, p, out + d.nslots, gate);
+    return LamPend{LAM_VALUE, out + d.nslots};
+  }
+  LamPend sten_pass(Ctx& c, int lev, int op, int mode, void* v, const void* r, void* out, const LamPend& in,
+                    const int* gate, const double* dot64) override {
+    if (c.fp32) return sten_pass_t<float>(c, lev, op, mode, (float*)v, (const float*)r, (float*)out, in, gate, dot64);
+    return sten_pass_t<double>(c, lev, op, mode, (double*)v, (const double*)r, (double*)out, in, gate, dot64);
+  }
+  void sten_jacobi0(Ctx& c, int lev, int op, const void* r, void* out, const int* gate) override {
+    const Level& l = c.lev[lev];
+    const int aug = op == IPMG_OP_Z;
+    const unsigned g = lin_grid(l.d.nslots + 1);
+    const double* omg = c.omega_dev + lev;
+    if (c.fp32)
+      k_sten_jacobi0<float><<<g, BS, 0, c.stream>>>((const float*)l.dinv, (const float*)r, (float*)out, l.d.nslots,
+                                                    omg, aug, c.cZ, gate);
+    else
+      k_sten_jacobi0<double><<<g, BS, 0, c.stream>>>((const double*)l.dinv, (const double*)r, (double*)out,
+                                                     l.d.nslots, omg, aug, c.cZ, gate);
+  }
+  void lam_store(Ctx& c, const LamPend& p, void* out, const int* gate) override {
+    if (c.fp32) k_lam_store<float><<<1, BS, 0, c.stream>>>(lam_ref<float>(c, p), (float*)out, gate);
+    else k_lam_store<double><<<1, BS, 0, c.stream>>>(lam_ref<double>(c, p), (double*)out, gate);
+  }
+
   void restrict_to(Ctx& c, int lev_f, const void* rf, void* rc, int aug, const int* gate) override {
     const Dims& f = c.lev[lev_f].d;
     const Dims& cd = c.lev[lev_f - 1].d;
     if (c.fp32)
-      k_restrict<DIM, float><<<node_grid(cd), BS, 0, c.stream>>>(f, cd, (const float*)rf, (float*)rc, aug, gate);
+      k_restrict<DIM, float><<<node_grid(cd), BS, 0, c.stream>>>(f, cd, (const float*)rf, (float*)rc, aug,
+                                                                 lam_ref<float>(c, c.lam_t), gate);
     else
-      k_restrict<DIM, double><<<node_grid(cd), BS, 0, c.stream>>>(f, cd, (const double*)rf, (double*)rc, aug, gate);
+      k_restrict<DIM, double><<<node_grid(cd), BS, 0, c.stream>>>(f, cd, (const double*)rf, (double*)rc, aug,
+                                                                  lam_ref<double>(c, c.lam_t), gate);
+    c.lam_t = LamPend{};
   }
   void restrict64(Ctx& c, int lev_f, const double* rf, double* rc) override {
     const Dims& f = c.lev[lev_f].d;
     const Dims& cd = c.lev[lev_f - 1].d;
-    k_restrict<DIM, double, double><<<node_grid(cd), BS, 0, c.stream>>>(f, cd, rf, rc, 0, nullptr);
+    k_restrict<DIM, double, double><<<node_grid(cd), BS, 0, c.stream>>>(f, cd, rf, rc, 0, LamRef<double>{}, nullptr);
   }
   void prolong_from(Ctx& c, int lev_f, void* z, const void* zc, int aug, const int* gate) override {
     const Dims& f = c.lev[lev_f].d;
     const Dims& cd = c.lev[lev_f - 1].d;
     if (c.fp32)
-      k_prolong<DIM, float><<<node_grid(f), BS, 0, c.stream>>>(f, cd, (float*)z, (const float*)zc, aug, gate);
+      k_prolong<DIM, float><<<node_grid(f), BS, 0, c.stream>>>(f, cd, (float*)z, (const float*)zc, aug,
+                                                               lam_ref<float>(c, c.lam_z), gate);
     else
-      k_prolong<DIM, double><<<node_grid(f), BS, 0, c.stream>>>(f, cd, (double*)z, (const double*)zc, aug, gate);
+      k_prolong<DIM, double><<<node_grid(f), BS, 0, c.stream>>>(f, cd, (double*)z, (const double*)zc, aug,
+                                                                lam_ref<double>(c, c.lam_z), gate);
+    c.lam_z = LamPend{};
   }
 
   bool fused_applies(const Ctx& c, int lev, int op) const override {
@@ -1187,7 +1482,7 @@ struct OpsImpl : Ops {
       // faster).  The first coarse level formed from the densities is VALU-bound:
       // fused (with its recomputed halos) it pays in FP32 only.
       const bool from_x = lev == c.L - 2 && c.coarse_from_x;
-      return c.fused2d && op == IPMG_OP_K && c.desc.nu_pre == 2 && c.desc.nu_post == 2 && lev >= 1 &&
+      return c.fused2d && lev > tail_level(c, op) && op == IPMG_OP_K && c.desc.nu_pre == 2 && c.desc.nu_post == 2 && lev >= 1 &&
              lev < c.L - 1 && (!from_x || c.fp32);
     }
   }

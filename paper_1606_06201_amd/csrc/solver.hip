@@ -17,16 +17,10 @@ namespace ipmg {
 
 namespace {
 
+// Device memory of the context (Ctx::arena): small buffers share slabs.
 template <typename P>
-void dalloc(P*& p, size_t bytes) {
-  void* q = nullptr;
-  if (hipMalloc(&q, bytes ? bytes : 8) != hipSuccess) throw Error(IPMG_E_NOMEM, "device allocation failed");
-  p = (P*)q;
-}
-template <typename P>
-void dfree(P*& p) {
-  if (p) (void)hipFree((void*)p);
-  p = nullptr;
+void dalloc(Ctx& c, P*& p, size_t bytes) {
+  p = (P*)c.arena.alloc(bytes);
 }
 
 // Safeguard of the Jacobi damping on every level except the coarsest:
@@ -85,29 +79,29 @@ static void ensure_z_buffers(Ctx& c) {
   if (c.h64) return;
   const Dims& d = c.fine();
   const size_t m = (size_t)d.m, n1 = (size_t)d.nslots + 1;
-  dalloc(c.h64, sizeof(double) * c.nd * m);
-  if (c.fp32) dalloc(c.hT, sizeof(float) * c.nd * m);
+  dalloc(c, c.h64, sizeof(double) * c.nd * m);
+  if (c.fp32) dalloc(c, c.hT, sizeof(float) * c.nd * m);
   else c.hT = c.h64;
-  dalloc(c.hsbuf, sizeof(double) * m);   // h_e'v_e of the operator pass in flight
-  dalloc(c.bZ64, sizeof(double) * n1);
-  if (c.fp32) dalloc(c.lev[c.L - 1].bZ, sizeof(float) * n1);
+  dalloc(c, c.hsbuf, sizeof(double) * m);   // h_e'v_e of the operator pass in flight
+  dalloc(c, c.bZ64, sizeof(double) * n1);
+  if (c.fp32) dalloc(c, c.lev[c.L - 1].bZ, sizeof(float) * n1);
   else c.lev[c.L - 1].bZ = c.bZ64;
   c.lev[c.L - 1].bZ64 = c.bZ64;
   for (int k = 0; k < c.L - 1; ++k) {
     const size_t nk = (size_t)c.lev[k].d.nslots + 1;
-    dalloc(c.lev[k].bZ64, sizeof(double) * nk);
-    if (c.fp32) dalloc(c.lev[k].bZ, sizeof(float) * nk);
+    dalloc(c, c.lev[k].bZ64, sizeof(double) * nk);
+    if (c.fp32) dalloc(c, c.lev[k].bZ, sizeof(float) * nk);
     else c.lev[k].bZ = c.lev[k].bZ64;
   }
-  dalloc(c.ipG3, sizeof(double) * m);
-  dalloc(c.ipW, sizeof(double) * m);
-  dalloc(c.ipSW, sizeof(double) * m);
-  dalloc(c.ipDx, sizeof(double) * m);
-  dalloc(c.ipDphi, sizeof(double) * m);
-  dalloc(c.ipDpsi, sizeof(double) * m);
-  dalloc(c.ipRhs, sizeof(double) * n1);
-  dalloc(c.ipD, sizeof(double) * n1);
-  dalloc(c.ipKu, sizeof(double) * n1);
+  dalloc(c, c.ipG3, sizeof(double) * m);
+  dalloc(c, c.ipW, sizeof(double) * m);
+  dalloc(c, c.ipSW, sizeof(double) * m);
+  dalloc(c, c.ipDx, sizeof(double) * m);
+  dalloc(c, c.ipDphi, sizeof(double) * m);
+  dalloc(c, c.ipDpsi, sizeof(double) * m);
+  dalloc(c, c.ipRhs, sizeof(double) * n1);
+  dalloc(c, c.ipD, sizeof(double) * n1);
+  dalloc(c, c.ipKu, sizeof(double) * n1);
 }
 
 void ctx_init(Ctx& c, const ipmg_desc& d, hipStream_t st) {
@@ -153,8 +147,6 @@ void ctx_init(Ctx& c, const ipmg_desc& d, hipStream_t st) {
   if (const char* e = std::getenv("IPMG_NO_FOLD_RN2")) c.fold_rn2_fin = e[0] != '1';
   if (const char* e = std::getenv("IPMG_NO_FOLD_RESTRICT")) c.fold_restrict = e[0] != '1';
   if (const char* e = std::getenv("IPMG_NO_ELEM_HV")) c.elem_hv = e[0] != '1';
-  if (const char* e = std::getenv("IPMG_NO_ELEM_APPLY3")) c.elem_apply3 = e[0] != '1';
-  if (const char* e = std::getenv("IPMG_ELEM_APPLY3_MIN")) c.elem_apply3_min = std::max<int64_t>(0, std::atoll(e));
   if (const char* e = std::getenv("IPMG_NO_ELEM_FINE3")) c.elem_fine3 = e[0] != '1';
   if (const char* e = std::getenv("IPMG_NO_MFMA")) c.mfma = e[0] != '1';
   if (const char* e = std::getenv("IPMG_NO_LANE_SHARE")) c.lane_share = e[0] != '1';
@@ -163,16 +155,22 @@ void ctx_init(Ctx& c, const ipmg_desc& d, hipStream_t st) {
   if (const char* e = std::getenv("IPMG_NJ32")) c.nj32 = std::atoi(e);
   if (const char* e = std::getenv("IPMG_NJ64")) c.nj64 = std::atoi(e);
   if (const char* e = std::getenv("IPMG_NJ_DIR")) c.nj_dir = std::atoi(e);
+  if (const char* e = std::getenv("IPMG_NO_TAIL")) c.tail_on = e[0] != '1';
+  // a path chosen for the coarse levels by one of these runs on all of them
+  for (const char* v : {"IPMG_STORED_COARSE", "IPMG_UNTILED", "IPMG_UNFUSED", "IPMG_UNSTAGED",
+                        "IPMG_STAGED_MAX_NODES", "IPMG_TILED_MIN_NODES", "IPMG_NO_MFMA", "IPMG_NO_FOLD_RESTRICT", "IPMG_NO_ELEM_FINE3",
+                        "IPMG_NO_ELEM_HV"})
+    if (std::getenv(v)) c.tail_on = false;
   c.power_steps = POWER_STEPS;
   c.power_steps_z = POWER_STEPS_Z;
   if (const char* e = std::getenv("IPMG_TILED_MIN_NODES")) c.tiled_min_nodes = std::max<int64_t>(0, std::atoll(e));
   c.ncoarse = (int)std::min<int64_t>(c.lev[0].d.nslots + 1, (int64_t)1 << 30);
 
   // reductions
-  dalloc(c.red.partials, sizeof(double) * 8 * MAX_PARTIALS);
-  dalloc(c.red.counter, sizeof(unsigned) * C_COUNT);
-  dalloc(c.red.scal, sizeof(double) * S_COUNT);
-  dalloc(c.red.flags, sizeof(int) * F_COUNT);
+  dalloc(c, c.red.partials, sizeof(double) * 8 * MAX_PARTIALS);
+  dalloc(c, c.red.counter, sizeof(unsigned) * C_COUNT);
+  dalloc(c, c.red.scal, sizeof(double) * S_COUNT);
+  dalloc(c, c.red.flags, sizeof(int) * F_COUNT);
   IPMG_HIP(hipMemsetAsync(c.red.counter, 0, sizeof(unsigned) * C_COUNT, st));
   IPMG_HIP(hipMemsetAsync(c.red.scal, 0, sizeof(double) * S_COUNT, st));
   IPMG_HIP(hipMemsetAsync(c.red.flags, 0, sizeof(int) * F_COUNT, st));
@@ -190,90 +188,63 @@ void ctx_init(Ctx& c, const ipmg_desc& d, hipStream_t st) {
   for (int k = 0; k < c.L; ++k) {
     Level& l = c.lev[k];
     const size_t n1 = (size_t)l.d.nslots + 1;
-    dalloc(l.r, c.tsz * n1);
-    dalloc(l.z, c.tsz * n1);
-    dalloc(l.z2, c.tsz * n1);
-    dalloc(l.t, c.tsz * n1);
+    dalloc(c, l.r, c.tsz * n1);
+    dalloc(c, l.z, c.tsz * n1);
+    dalloc(c, l.z2, c.tsz * n1);
+    dalloc(c, l.t, c.tsz * n1);
     IPMG_HIP(hipMemsetAsync(l.z, 0, c.tsz * n1, st));
     IPMG_HIP(hipMemsetAsync(l.z2, 0, c.tsz * n1, st));
     if (k < c.L - 1) {
-      dalloc(l.E64, sizeof(double) * (size_t)nsym * (size_t)l.d.m);
-      if (c.fp32) dalloc(l.E, sizeof(float) * (size_t)nsym * (size_t)l.d.m);
-      else l.E = l.E64;
+      dalloc(c, l.E64, sizeof(double) * (size_t)nsym * (size_t)l.d.m);
+      if (!c.fp32) l.E = l.E64;
+      else if (c.ops->needs_elements(c, k, IPMG_OP_K) || c.ops->needs_elements(c, k, IPMG_OP_Z))
+        dalloc(c, l.E, sizeof(float) * (size_t)nsym * (size_t)l.d.m);
     }
   }
   // Densities, followed by a zero pad of nx + 2 entries: kernels read an element
   // outside the grid (or a 2 x 2 block of them) there instead of branching.
   const int64_t xn = fd.m + fd.nx + 2;
-  dalloc(c.x64, sizeof(double) * xn);
+  dalloc(c, c.x64, sizeof(double) * xn);
   IPMG_HIP(hipMemsetAsync(c.x64, 0, sizeof(double) * xn, st));
   if (c.fp32) {
-    dalloc(c.xT, sizeof(float) * xn);
+    dalloc(c, c.xT, sizeof(float) * xn);
     IPMG_HIP(hipMemsetAsync(c.xT, 0, sizeof(float) * xn, st));
   } else {
     c.xT = c.x64;
   }
   const size_t n1 = (size_t)fd.nslots + 1;
-  dalloc(c.pr, sizeof(double) * n1);
-  dalloc(c.pp, sizeof(double) * n1);
-  dalloc(c.pq, sizeof(double) * n1);
-  dalloc(c.pt, sizeof(double) * n1);
-  dalloc(c.pb, sizeof(double) * n1);
-  dalloc(c.pu, sizeof(double) * n1);
-  dalloc(c.pp2, sizeof(double) * n1);
+  dalloc(c, c.pr, sizeof(double) * n1);
+  dalloc(c, c.pp, sizeof(double) * n1);
+  dalloc(c, c.pq, sizeof(double) * n1);
+  dalloc(c, c.pt, sizeof(double) * n1);
+  dalloc(c, c.pb, sizeof(double) * n1);
+  dalloc(c, c.pu, sizeof(double) * n1);
+  dalloc(c, c.pp2, sizeof(double) * n1);
   vfill(st, c.pp, 0.0, (int64_t)n1);    // the direction kernel reads p_old (times 0) on the first iteration
   vfill(st, c.pp2, 0.0, (int64_t)n1);
-  dalloc(c.omega_dev, sizeof(double) * 2 * c.L);
-  dalloc(c.oc_cand, sizeof(double) * OC_CAND);
-  if (d.dim == 3 && c.L >= 2 && c.elem_apply3) dalloc(c.ye, c.tsz * 24 * (size_t)c.lev[c.L - 2].d.m);
+  dalloc(c, c.omega_dev, sizeof(double) * 2 * c.L);
+  dalloc(c, c.oc_cand, sizeof(double) * OC_CAND);
   if (d.dim == 3 && c.elem_fine3) {
-    dalloc(c.fine_ye64, sizeof(double) * 24 * (size_t)fd.m);
-    if (c.fp32) dalloc(c.fine_ye, sizeof(float) * 24 * (size_t)fd.m);
+    dalloc(c, c.fine_ye64, sizeof(double) * 24 * (size_t)fd.m);
+    if (c.fp32) dalloc(c, c.fine_ye, sizeof(float) * 24 * (size_t)fd.m);
     else c.fine_ye = c.fine_ye64;
-    dalloc(c.fine_dg, c.tsz * (size_t)fd.nslots);
+    dalloc(c, c.fine_dg, c.tsz * (size_t)fd.nslots);
   }
   vfill_small(st, c.omega_dev, c.L, d.omega);
 
   // element matrix on the GPU, mirrored to the host and to constant memory
   double* dK0 = nullptr;
-  dalloc(dK0, sizeof(double) * c.nd * c.nd);
+  dalloc(c, dK0, sizeof(double) * c.nd * c.nd);
   c.ops->element_stiffness(c, dK0);
   IPMG_HIP(hipGetLastError());
   IPMG_HIP(hipMemcpyAsync(c.K0, dK0, sizeof(double) * c.nd * c.nd, hipMemcpyDeviceToHost, st));
   sync(c);
-  dfree(dK0);
   c.ops->upload_k0(c.K0);
 }
 
 void ctx_free(Ctx& c) {
   if (c.stream) (void)hipStreamSynchronize(c.stream);
-  for (auto& l : c.lev) {
-    dfree(l.r); dfree(l.z); dfree(l.z2); dfree(l.t);
-    if (l.E != (void*)l.E64) dfree(l.E);
-    l.E = nullptr;
-    dfree(l.E64);
-    if (l.bZ != (void*)l.bZ64 && l.bZ != (void*)c.bZ64) dfree(l.bZ);
-    l.bZ = nullptr;
-    if (l.bZ64 != c.bZ64) dfree(l.bZ64);
-    l.bZ64 = nullptr;
-  }
-  if (c.xT != (void*)c.x64) dfree(c.xT);
-  c.xT = nullptr;
-  if (c.hT != (void*)c.h64) dfree(c.hT);
-  c.hT = nullptr;
-  dfree(c.x64); dfree(c.h64); dfree(c.bZ64); dfree(c.hsbuf);
-  dfree(c.pr); dfree(c.pp); dfree(c.pq); dfree(c.pt); dfree(c.pb); dfree(c.pu); dfree(c.pp2);
-  dfree(c.dA); dfree(c.dLi); dfree(c.dAi); dfree(c.dAif); dfree(c.dpart); dfree(c.omega_dev);
-  dfree(c.red.partials); dfree(c.red.counter); dfree(c.red.scal); dfree(c.red.flags);
-  dfree(c.ipG3); dfree(c.ipW); dfree(c.ipSW); dfree(c.ipDx); dfree(c.ipDphi); dfree(c.ipDpsi);
-  dfree(c.ipRhs); dfree(c.ipD); dfree(c.ipKu);
-  dfree(c.oc_t); dfree(c.oc_cand); dfree(c.ye); dfree(c.simp_xt); dfree(c.simp_xp);
-  for (double** b : {&c.simp_cf, &c.simp_g, &c.simp_E, &c.simp_a, &c.simp_t, &c.simp_b1, &c.simp_b2, &c.simp_b3,
-                     &c.simp_bcoef, &c.simp_rcoef, &c.simp_r, &c.simp_y, &c.simp_p, &c.simp_q})
-    dfree(*b);
-  if (c.fine_ye != (void*)c.fine_ye64) dfree(c.fine_ye);
-  c.fine_ye = nullptr;
-  dfree(c.fine_ye64); dfree(c.fine_dg);
+  c.arena.release();
   if (c.hscal) (void)hipHostFree(c.hscal);
   if (c.hflags) (void)hipHostFree(c.hflags);
   c.hscal = nullptr; c.hflags = nullptr;
@@ -321,16 +292,24 @@ static void jacobi_damping(Ctx& c, int k, int op, int steps, double product) {
   vset_omega(c.stream, c.red, c.omega_dev + k, c.omega_dev + c.L + k, S_TMP6, S_TMP7, c.desc.omega, product);
 }
 
+// Damping of every level above the coarsest.
+static void damping_all(Ctx& c, int op, int steps, double product) {
+  c.ops->sten_damping(c, op, steps, product);
+  for (int k = 1; k < c.L; ++k)
+    if (!c.ops->sten_level(c, k, op)) jacobi_damping(c, k, op, steps, product);
+}
+
 static void ensure_dense(Ctx& c) {
   if (c.dA) return;
   const int64_t n = c.lev[0].d.nslots + 1;
   IPMG_REQUIRE(n <= DENSE_MAX_N, IPMG_E_INVALID, "coarsest level too large for the dense solve; use more levels");
   const int64_t np = dense_packed_size((int)n), nt = dense_tiles((int)n);
-  dalloc(c.dA, sizeof(double) * np);
-  dalloc(c.dLi, sizeof(double) * np);
-  dalloc(c.dAi, sizeof(double) * np);
-  if (c.fp32) dalloc(c.dAif, sizeof(float) * np);
-  dalloc(c.dpart, sizeof(double) * nt * nt * DT);
+  dalloc(c, c.dA, sizeof(double) * np);
+  dalloc(c, c.dLi, sizeof(double) * np);
+  dalloc(c, c.dAi, sizeof(double) * np);
+  if (c.fp32) dalloc(c, c.dAif, sizeof(float) * np);
+  dalloc(c, c.dpart, sizeof(double) * nt * nt * DT);
+  if (c.ops->tail_level(c, IPMG_OP_K) > 0 && nt * DT <= TAIL_MAX_LD) dalloc(c, c.dfull, c.tsz * (size_t)(nt * DT * nt * DT));
 }
 
 void mg_setup(Ctx& c, int op, double* ms) {
@@ -344,7 +323,8 @@ void mg_setup(Ctx& c, int op, double* ms) {
   for (int k = L - 1; k >= 1; --k) {
     Level& lc = c.lev[k - 1];
     c.ops->galerkin(c, k, op);                       // FP64 chain
-    if (c.fp32) vconvert<float, double>(c.stream, lc.E64, (float*)lc.E, (int64_t)nsym * lc.d.m, nullptr);
+    if (c.fp32 && c.ops->needs_elements(c, k - 1, op))
+      vconvert<float, double>(c.stream, lc.E64, (float*)lc.E, (int64_t)nsym * lc.d.m, nullptr);
     if (op == IPMG_OP_Z) {
       c.ops->restrict64(c, k, c.lev[k].bZ64, lc.bZ64);
       if (c.fp32) vconvert<float, double>(c.stream, lc.bZ64, (float*)lc.bZ, lc.d.nslots, nullptr);
@@ -352,14 +332,15 @@ void mg_setup(Ctx& c, int op, double* ms) {
   }
   IPMG_HIP(hipGetLastError());
   ensure_dense(c);
-  c.ops->fine_diag(c, op);
+  if (!c.ops->sten_level(c, L - 1, op)) c.ops->fine_diag(c, op);
+  c.ops->sten_setup(c, op);
   const int steps = op == IPMG_OP_Z ? c.power_steps_z : c.power_steps;
-  for (int k = 1; k < L; ++k) jacobi_damping(c, k, op, steps, SAFE_PRODUCT);
+  damping_all(c, op, steps, SAFE_PRODUCT);
   const int n = c.lev[0].d.nslots + (op == IPMG_OP_Z ? 1 : 0);
   IPMG_HIP(hipMemsetAsync(c.red.flags + F_BAD, 0, sizeof(int), c.stream));
   dense_init(c.stream, c.dA, n, 1);
   c.ops->dense_assemble(c, op, c.dA, n);
-  dense_factor_inverse(c.stream, c.dA, c.dLi, c.dAi, n, c.red, c.dAif);
+  dense_factor_inverse(c.stream, c.dA, c.dLi, c.dAi, n, c.red, c.dAif, c.dfull, c.fp32 ? 1 : 0);
   IPMG_HIP(hipGetLastError());
   read_scalars(c);
   IPMG_REQUIRE(!c.hflags[F_BAD], IPMG_E_BREAKDOWN, "coarsest operator is not positive definite");
@@ -379,9 +360,72 @@ static void rn2_fin_flush(Ctx& c, const int* gate) {
   c.rn2_fin_blocks = 0;
 }
 
+static void* vcycle_level(Ctx& c, int op, int k, const int* gate, const double* beta64);
+
+// Level k in node-stencil form.  The lambda entry of each pass's result is found by
+// whatever reads it next (LamPend).
+static void* vcycle_sten(Ctx& c, int op, int k, const int* gate, const double* beta64) {
+  Level& l = c.lev[k];
+  const int aug = op == IPMG_OP_Z;
+  const bool fine = k == c.L - 1;
+  const int64_t n = l.d.nslots;
+  const size_t tsz = c.tsz;
+  auto stored = [&](void* v) {
+    LamPend p;
+    if (aug) {
+      p.kind = 1;                                     // LAM_VALUE
+      p.value = (const char*)v + tsz * (size_t)n;
+    }
+    return p;
+  };
+  rn2_fin_flush(c, gate);
+  void* cur = l.z;
+  void* nxt = l.z2;
+  LamPend lam;
+  int s = 1;
+  if (c.desc.nu_pre >= 2 && c.ops->sten_fuses_two(c, k, op)) {
+    ProfTag pt(c, fine ? PC_FINE_JACOBI2 : -1);
+    lam = c.ops->sten_pass(c, k, op, SP_JACOBI2, nullptr, l.r, cur, LamPend{}, gate, nullptr);
+    s = 2;
+  } else {
+    c.ops->sten_jacobi0(c, k, op, l.r, cur, gate);
+    lam = stored(cur);
+  }
+  for (; s < c.desc.nu_pre; ++s) {
+    ProfTag pt(c, fine ? PC_FINE_JACOBI : (k == c.L - 2 ? PC_SUB_JACOBI : -1));
+    lam = c.ops->sten_pass(c, k, op, SP_JACOBI, cur, l.r, nxt, lam, gate, nullptr);
+    std::swap(cur, nxt);
+  }
+  {
+    ProfTag pt(c, fine ? PC_FINE_RESID : -1);
+    c.lam_t = c.ops->sten_pass(c, k, op, SP_RESID, cur, l.r, l.t, lam, gate, nullptr);
+  }
+  if (c.lam_t.kind == 1) c.lam_t = LamPend{};         // stored with the vector
+  c.ops->restrict_to(c, k, l.t, c.lev[k - 1].r, aug, gate);
+  void* vc = vcycle_level(c, op, k - 1, gate, nullptr);
+  c.ops->prolong_from(c, k, cur, vc, aug, gate);
+  lam = stored(cur);
+  for (int q = 0; q < c.desc.nu_post; ++q) {
+    const bool last = beta64 && q == c.desc.nu_post - 1;
+    ProfTag pt(c, last ? (fine ? PC_FINE_JACOBI_BETA : -1) : (fine ? PC_FINE_JACOBI : (k == c.L - 2 ? PC_SUB_JACOBI : -1)));
+    lam = c.ops->sten_pass(c, k, op, last ? SP_BETA : SP_JACOBI, cur, l.r, nxt, lam, gate, last ? beta64 : nullptr);
+    std::swap(cur, nxt);
+  }
+  if (aug && lam.kind > 1) {
+    if (fine) c.ops->lam_store(c, lam, (char*)cur + tsz * (size_t)n, gate);
+    else c.lam_z = lam;                               // the prolongation adds the partials
+  }
+  return cur;
+}
+
 static void* vcycle_level(Ctx& c, int op, int k, const int* gate, const double* beta64) {
   Level& l = c.lev[k];
   const int aug = op == IPMG_OP_Z;
+  if (k >= 1 && k == c.ops->tail_level(c, op)) {
+    c.ops->tail(c, op, gate, beta64);
+    return l.z;
+  }
+  if (c.ops->sten_level(c, k, op)) return vcycle_sten(c, op, k, gate, beta64);
   if (c.rn2_fin_blocks && (k == 0 || c.ops->fused_applies(c, k, op) || c.desc.nu_pre < 2)) rn2_fin_flush(c, gate);
   if (k == 0) {
     const int n = l.d.nslots + aug;
@@ -456,7 +500,10 @@ static void* vcycle_level(Ctx& c, int op, int k, const int* gate, const double* 
 // Work a previous call left pending when it stopped on an error is dropped.
 static void clear_pending(Ctx& c) {
   c.rn2_fin_blocks = 0;
+  c.step_in_tail = false;
+  c.step_blocks = 0;
   c.down_from_t = nullptr;
+  c.lam_t = c.lam_z = LamPend{};
 }
 
 void* vcycle(Ctx& c, int op, const int* gate) {
@@ -485,7 +532,17 @@ void vcycle64(Ctx& c, int op, const double* r, double* z) {
 // `first` selects beta = 0 (first step after a (re)start).
 // With the fold, z += alpha p of a step is done by the next step's direction
 // kernel (which reads that p anyway) and, for the last step, by vzflush.
+// With the finest level in the one-workgroup tail, the tail's launch does all that
+// follows the direction kernel.
 static void pcg_iteration(Ctx& c, int op, int64_t n, const int* gate, int first) {
+  if (c.ops->tail_level(c, op) == c.L - 1 && c.L > 1) {
+    c.step_in_tail = true;
+    c.ops->dir_apply(c, op, c.yT, c.pp, c.pp2, c.pq, first, gate, nullptr);
+    c.step_in_tail = false;
+    std::swap(c.pp, c.pp2);
+    c.yT = vcycle_level(c, op, c.L - 1, gate, c.pr);
+    return;
+  }
   const bool fold = c.ops->dir_folds_solution(c);
   c.ops->dir_apply(c, op, c.yT, c.pp, c.pp2, c.pq, first, gate, fold ? c.pu : nullptr);
   std::swap(c.pp, c.pp2);                                               // c.pp holds the new p
@@ -692,7 +749,7 @@ int pcg_noalloc(Ctx& c, int op, const double* b, double* u, double rtol, int max
 void oc_update(Ctx& c, const double* u, const double* x, double V, double xbar, double q, double lam_hi,
                double tau, const double* blend, double* x_new, ipmg_oc_info* info) {
   const Dims& d = c.fine();
-  if (!c.oc_t) dalloc(c.oc_t, sizeof(double) * (size_t)d.m);
+  if (!c.oc_t) dalloc(c, c.oc_t, sizeof(double) * (size_t)d.m);
   c.ops->oc_energy(c, u, x, q, c.oc_t);
   voc_init(c.stream, c.red, c.oc_cand, lam_hi);
   // trials of sequential bisection in exact arithmetic, plus two for rounding;
@@ -721,8 +778,8 @@ void oc_update(Ctx& c, const double* u, const double* x, double V, double xbar, 
 int simp_compliance(Ctx& c, const double* x, const double* f, double rmin, double p, double rtol, int maxit,
                     double* u, double* grad, ipmg_pcg_info* info) {
   const Dims& d = c.fine();
-  if (!c.simp_xt) dalloc(c.simp_xt, sizeof(double) * (size_t)d.m);
-  if (!c.simp_xp) dalloc(c.simp_xp, sizeof(double) * (size_t)d.m);
+  if (!c.simp_xt) dalloc(c, c.simp_xt, sizeof(double) * (size_t)d.m);
+  if (!c.simp_xp) dalloc(c, c.simp_xp, sizeof(double) * (size_t)d.m);
   c.ops->filter(c, rmin, x, c.simp_xt, 0);
   c.ops->simp_pow(c, c.simp_xt, p, c.simp_xp, nullptr);
   IPMG_HIP(hipGetLastError());
@@ -744,13 +801,13 @@ static void ensure_simp_buffers(Ctx& c) {
   if (c.simp_cf) return;
   const Dims& d = c.fine();
   const size_t m = (size_t)d.m, n1 = (size_t)d.nslots + 1;
-  if (!c.simp_xt) dalloc(c.simp_xt, sizeof(double) * m);
-  if (!c.simp_xp) dalloc(c.simp_xp, sizeof(double) * m);
+  if (!c.simp_xt) dalloc(c, c.simp_xt, sizeof(double) * m);
+  if (!c.simp_xp) dalloc(c, c.simp_xp, sizeof(double) * m);
   for (double** b : {&c.simp_cf, &c.simp_E, &c.simp_a, &c.simp_t, &c.simp_b1, &c.simp_b2, &c.simp_b3, &c.simp_bcoef,
                      &c.simp_rcoef})
-    dalloc(*b, sizeof(double) * m);
-  dalloc(c.simp_g, sizeof(double) * (size_t)c.nd * m);
-  for (double** b : {&c.simp_r, &c.simp_y, &c.simp_p, &c.simp_q}) dalloc(*b, sizeof(double) * n1);
+    dalloc(c, *b, sizeof(double) * m);
+  dalloc(c, c.simp_g, sizeof(double) * (size_t)c.nd * m);
+  for (double** b : {&c.simp_r, &c.simp_y, &c.simp_p, &c.simp_q}) dalloc(c, *b, sizeof(double) * n1);
 }
 
 // x~ = W x, K^ = sum x~^p K_e (set as the densities), c = p x~^(p-1).
@@ -910,8 +967,7 @@ int simp_ip_step(Ctx& c, const double* f, const ipmg_ip_params& p, double rmin, 
   if (ps == IPMG_E_BREAKDOWN) {   // as ip_step: damping estimated again, continued from the last iterate
     const int first = pin.iters;
     const double first_ms = pin.solve_ms;
-    for (int k = 1; k < c.L; ++k)
-      jacobi_damping(c, k, IPMG_OP_Z, RETRY_POWER_FACTOR * c.power_steps_z, SAFE_PRODUCT_RETRY);
+    damping_all(c, IPMG_OP_Z, RETRY_POWER_FACTOR * c.power_steps_z, SAFE_PRODUCT_RETRY);
     IPMG_HIP(hipGetLastError());
     ps = simp_pcg(c, rmin, st.u, c.ipRhs, c.ipD, p.pcg_rtol, p.pcg_maxit, true, &pin);
     pin.iters += first;
@@ -1017,8 +1073,7 @@ int ip_step(Ctx& c, const double* f, const ipmg_ip_params& p, ipmg_ip_state& st,
   if (ps == IPMG_E_BREAKDOWN) {
     const int first = pin.iters;
     const double first_ms = pin.solve_ms;
-    for (int k = 1; k < c.L; ++k)
-      jacobi_damping(c, k, IPMG_OP_Z, RETRY_POWER_FACTOR * c.power_steps_z, SAFE_PRODUCT_RETRY);
+    damping_all(c, IPMG_OP_Z, RETRY_POWER_FACTOR * c.power_steps_z, SAFE_PRODUCT_RETRY);
     IPMG_HIP(hipGetLastError());
     ps = pcg(c, IPMG_OP_Z, c.ipRhs, c.ipD, p.pcg_rtol, p.pcg_maxit, &pin);
     pin.iters += first;
