@@ -925,7 +925,9 @@ __device__ inline void level_node(const Op& op, const Dims& d, int i, int j, int
     }
     T acc[3] = {T(0), T(0), T(0)}, dg[3] = {T(0), T(0), T(0)}, vc[3] = {T(0), T(0), T(0)};
     if constexpr (MODE != M_JACOBI0) load_node<3, T>(v, q, vc);
-    node_apply_gather3<T, Op, MODE != M_JACOBI0, true>(op, d, i, j, k, v, acc, dg);
+    // no diagonal where the pass has none: a product or a residual then takes its rows
+    // from the element products whether or not the set-up diagonal is at hand
+    node_apply_gather3<T, Op, MODE != M_JACOBI0, MODE != M_APPLY && MODE != M_RESID>(op, d, i, j, k, v, acc, dg);
     level_node_finish<3, T, MODE>(q, acc, dg, vc, r, out, omega, augb, vl, pin, dot64, bdot, red0, red1);
   } else {
     T vn[Geo<DIM>::NB][DIM];
@@ -2450,6 +2452,89 @@ __device__ inline void galerkin_scatter_q(int q, const double* t, double* row) {
         }
       }
   }
+}
+
+// First coarse level of the 3D augmented system: A_C = sum_q (x_q G_q + g_q g_q'), with
+// the constant images G_q = W_q' K0 W_q of the unit element and g_q = W_q' h_q.  A
+// block takes 64 coarse elements: wave q forms g_q of all of them into LDS (every h_e
+// read once), then wave w sums rows w, 15-w and 16+w (34 to
+// 41 stored entries) over the eight sub-elements.  The row form above reads
+// every h_e once per coarse row, 24 times; at 64 x 32 x 32 coarse elements it took
+// 752 us for 257 MB of necessary traffic.
+// LDS: 8 x 24 x 64 doubles of g and 8 x 64 densities, 100 KB.  Below 64 coarse
+// elements a wave would not be full, and the row form spreads over six blocks.
+constexpr int GZ3_THREADS = 512;
+static __constant__ double cG3d[8 * 576];
+template <int Q>
+__device__ inline void galerkin_gq3(const double* h, double* g) {
+#pragma unroll
+  for (int t = 0; t < 24; ++t) g[t] = 0.0;
+  galerkin_scatter<3, Q>(h, g);
+}
+static __global__ __launch_bounds__(GZ3_THREADS) void k_galerkin_z3(const double* __restrict__ x,
+                                                                     const double* __restrict__ h, Dims f, Dims c,
+                                                                     double* __restrict__ Ec) {
+  __shared__ double G[8][24][64];
+  __shared__ double X[8][64];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t C0 = (int64_t)xcd_tile().x * 64 + lane, C = C0 < c.m ? C0 : c.m - 1;
+  const int CI = (int)(C % c.nx), CJ = (int)((C / c.nx) % c.ny), CK = (int)(C / ((int64_t)c.nx * c.ny));
+  {
+    const int qx = w & 1, qy = (w >> 1) & 1, qz = w >> 2;
+    const int64_t e = ((int64_t)(2 * CK + qz) * f.ny + (2 * CJ + qy)) * f.nx + (2 * CI + qx);
+    double hv[24], g[24];
+#pragma unroll
+    for (int t = 0; t < 24; ++t) hv[t] = h[(int64_t)t * f.m + e];
+    X[w][lane] = x[e];
+    switch (w) {
+      case 0: galerkin_gq3<0>(hv, g); break;
+      case 1: galerkin_gq3<1>(hv, g); break;
+      case 2: galerkin_gq3<2>(hv, g); break;
+      case 3: galerkin_gq3<3>(hv, g); break;
+      case 4: galerkin_gq3<4>(hv, g); break;
+      case 5: galerkin_gq3<5>(hv, g); break;
+      case 6: galerkin_gq3<6>(hv, g); break;
+      default: galerkin_gq3<7>(hv, g); break;
+    }
+#pragma unroll
+    for (int t = 0; t < 24; ++t) G[w][t][lane] = g[t];
+  }
+  __syncthreads();
+  double xq[8], gr[3][8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    xq[q] = X[q][lane];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) gr[u][q] = G[q][u == 0 ? w : (u == 1 ? 15 - w : 16 + w)][lane];
+  }
+  for (int col = w; col < 24; ++col) {
+    double gc[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) gc[q] = G[q][col][lane];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      const int R = u == 0 ? w : (u == 1 ? 15 - w : 16 + w);
+      if (col < R) continue;
+      double sk = 0.0, sh = 0.0;              // the stiffness and the rank-one part
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        sk = fma(xq[q], cG3d[(q * 24 + R) * 24 + col], sk);
+        sh = fma(gr[u][q], gc[q], sh);
+      }
+      if (C0 < c.m) Ec[(int64_t)sym_index(R, col, 24) * c.m + C] = sk + sh;
+    }
+  }
+}
+// The images G_q of the unit cube element (one thread per entry).
+static __global__ void k_galerkin_images3d(const double* __restrict__ K0, double* __restrict__ G) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= 8 * 576) return;
+  const int q = t / 576, r = t / 24 % 24, cc = t % 24;
+  double s = 0.0;
+  for (int a = 0; a < 8; ++a)
+    for (int b = 0; b < 8; ++b)
+      s += row_weight<3>(q, a, r / 3) * row_weight<3>(q, b, cc / 3) * K0[(a * 3 + r % 3) * 24 + b * 3 + cc % 3];
+  G[t] = s;
 }
 
 constexpr int GAL_WAVES = 4;

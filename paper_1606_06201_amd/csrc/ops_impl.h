@@ -694,6 +694,16 @@ struct OpsImpl : Ops {
       for (int t = 0; t < 14; ++t) k14f[t] = (float)k14[t];
       IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cK3d), k14, sizeof(double) * 14));
       IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cK3f), k14f, sizeof(float) * 14));
+      double *dK = nullptr, *dG = nullptr;
+      IPMG_HIP(hipMalloc((void**)&dK, sizeof(double) * 576));
+      IPMG_HIP(hipMalloc((void**)&dG, sizeof(double) * 8 * 576));
+      IPMG_HIP(hipMemcpy(dK, K0, sizeof(double) * 576, hipMemcpyHostToDevice));
+      k_galerkin_images3d<<<8 * 576 / 64, 64>>>(dK, dG);
+      std::vector<double> G(8 * 576);
+      IPMG_HIP(hipMemcpy(G.data(), dG, sizeof(double) * 8 * 576, hipMemcpyDeviceToHost));
+      (void)hipFree(dK);
+      (void)hipFree(dG);
+      IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cG3d), G.data(), sizeof(double) * 8 * 576));
     }
     float kf[576];
     for (int t = 0; t < ND * ND; ++t) kf[t] = (float)K0[t];
@@ -1660,6 +1670,8 @@ struct OpsImpl : Ops {
     double* Ec = c.lev[lev_f - 1].E64;
     if (lev_f == c.L - 1) {
       if (op == IPMG_OP_K) launch_galerkin(c, OpFineK<DIM, double>{c.x64, f.m}, f, cd, Ec);
+      else if (DIM == 3 && cd.m >= 64)   // a full wave of coarse elements
+        k_galerkin_z3<<<(unsigned)((cd.m + 63) / 64), GZ3_THREADS, 0, c.stream>>>(c.x64, c.h64, f, cd, Ec);
       else launch_galerkin(c, OpFineZ<DIM, double>{c.x64, c.h64, f.m}, f, cd, Ec);
     } else {
       launch_galerkin(c, OpCoarse<DIM, double>{c.lev[lev_f].E64, f.m}, f, cd, Ec);
