@@ -190,7 +190,7 @@ def bench_3d_section(dev, steps=8, cpu=True):
     s = Solver(nel, levels, fp32=True, device=dev)
     f = s.load_vector(inputs.point_load(nel))
     params = s.ip_params(0.3 * s.m, 1.0, stop="kkt", kkt_tol=1e-6)
-    names = ["dir_apply", "fine_jacobi", "fine_jacobi0", "fine_resid", "fine_jacobi_beta", "elem3", "elem3_dir"]
+    names = ["dir_apply", "fine_jacobi", "fine_jacobi0", "fine_resid", "fine_jacobi_beta", "fine_jacobi2"]
     st, _ = s.ip_init(f, params)
     s.ip_step(f, params, st)                           # warm-up step (untimed)
     s.profile_begin(names, max_launches=8000)
@@ -213,25 +213,19 @@ def bench_3d_section(dev, steps=8, cpu=True):
         d = d[d > 0.5 * np.median(d)]
         if len(d):
             avg[k] = (float(d.mean()), int(len(d)))
-    # A finest-level operator pass is an element-product launch (elem3 / elem3_dir)
-    # followed by its node pass; both count toward the pass's time.
+    # A finest-level operator pass forms the element products and the node sums in one launch.
     kern = {}
-    for k in ("dir_apply", "fine_jacobi", "fine_jacobi0", "fine_resid", "fine_jacobi_beta"):
+    for k in ("dir_apply", "fine_jacobi", "fine_jacobi0", "fine_jacobi2", "fine_resid", "fine_jacobi_beta"):
         if k not in avg:
             continue
         a, n = avg[k]
-        pre = 0.0
-        if k == "dir_apply" and "elem3_dir" in avg:
-            pre = avg["elem3_dir"][0]
-        elif k != "fine_jacobi0" and "elem3" in avg:         # the first sweep from zero reads no vector
-            pre = avg["elem3"][0]
-        t = a + pre
+        t = a
         fl = fl_z if k != "fine_jacobi0" else 2 * 24 * m     # from zero: the diagonal scaling only
         # published vector peaks: FP64 78.6 TFLOP/s (the direction kernel), FP32
         # 157.3 (the V-cycle sweeps; 78.6 without packed FP32 instructions, which
         # this library does not emit)
         peak = 78.6 if k == "dir_apply" else 157.3
-        kern[k] = {"avg_us": 1000 * t, "node_pass_us": 1000 * a, "element_pass_us": 1000 * pre, "launches": n,
+        kern[k] = {"avg_us": 1000 * t, "launches": n,
                    "flops": fl, "TFLOP_per_s": fl / (t * 1e-3) / 1e12, "peak_TFLOP_per_s": peak,
                    "frac": fl / (t * 1e-3) / 1e12 / peak, "dtype": "f64" if k == "dir_apply" else "f32"}
     dom = max(kern, key=lambda k: kern[k]["avg_us"] * kern[k]["launches"]) if kern else None

@@ -315,11 +315,9 @@ int ipmg_simp_ip_step(ipmg_ctx* ctx, const double* f, const ipmg_ip_params* prm,
  *   6: last post-smoothing sweep on the finest level with the fused PCG ratio
  *   7: fused pre-smoothing, residual and restriction on the first coarse level
  *   8: fused prolongation and post-smoothing on the first coarse level
- *   9, 10: reserved (no kernel records them)
+ *   9, 10, 13, 14: reserved (no kernel records them)
  *  11: prolongation folded into the first post-smoothing sweep on the finest level
  *  12: the first two pre-smoothing sweeps on the finest level in one pass
- *  13: 3D finest level, element products of a V-cycle pass (before its node pass)
- *  14: 3D finest level, element products of the FP64 PCG direction
  * Launches skipped on device after convergence are recorded too (with near-zero
  * duration).  max_launches: event pairs to keep (further launches are not timed).
  * durations_ms: [host] capacity entries, each launch's duration; classes: [host,

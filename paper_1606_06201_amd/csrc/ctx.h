@@ -228,7 +228,7 @@ struct Ctx {
   double* h64 = nullptr;       // Z rank-one factors h_e (ND * m)
   void* hT = nullptr;
   void* hsbuf = nullptr;       // per-element h_e'v_e (m values, FP64 or FP32) for the 3D Z passes
-  bool elem_hv = true;         // form h_e'v_e per element before each 3D Z pass
+  bool elem_hv = true;         // gather form of the 3D Z passes: form h_e'v_e per element first
   double* bZ64 = nullptr;      // border of Z on the finest grid (n_slots)
   double cZ = 0.0;             // corner of Z
   bool have_x = false;
@@ -273,10 +273,9 @@ struct Ctx {
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   std::string err;
 
-  // 3D finest level: element products of the pass's vector (V-cycle precision and
-  // FP64, aliased in FP64 mode) and the set-up diagonal
-  void* fine_ye = nullptr;
-  double* fine_ye64 = nullptr;
+  // 3D finest level: the set-up diagonal; for Z the displacements (0 on clamped
+  // slots) whose K0 u_e, scaled by ipSW, is the rank-one factor h_e
+  double* hu = nullptr;
   void* fine_dg = nullptr;
   bool elem_fine3 = true;
 
@@ -322,8 +321,7 @@ enum ProfClass {
   // 9 and 10: reserved (no kernel records them)
   PC_FINE_PJACOBI = 11,     // finest level, prolongation folded into the first post-smoothing sweep
   PC_FINE_JACOBI2 = 12,     // finest level, the first two pre-smoothing sweeps in one pass
-  PC_ELEM3 = 13,            // 3D finest level, element products of a V-cycle pass
-  PC_ELEM3_DIR = 14,        // 3D finest level, element products of the FP64 direction
+  // 13 and 14: reserved (no kernel records them)
   PC_COUNT = 15
 };
 

@@ -249,8 +249,6 @@ template <int DIM, typename T>
 struct OpFineK {
   const T* x;
   int64_t m;
-  const T* ye = nullptr;    // 3D: element products of the pass's vector (k_elem_fine3e)
-  const T* dgn = nullptr;   // 3D: the diagonal per DOF slot, formed at set-up (k_fine_diag3)
   __device__ inline void rows(int64_t e, int, int, int, int a, const T* ve, T* acc) const {
     constexpr int ND = Geo<DIM>::ND;
     const T xe = x[e];
@@ -283,8 +281,6 @@ struct OpFineZ {
   const T* h;
   int64_t m;
   const T* hs = nullptr;   // h_e'v_e per element, formed beforehand by k_elem_hv (same sum)
-  const T* ye = nullptr;   // 3D: element products of the pass's vector (k_elem_fine3e)
-  const T* dgn = nullptr;  // 3D: the diagonal per DOF slot, formed at set-up (k_fine_diag3)
   // rows() sums h_e'v_e over ve itself: its callers may map an element outside the
   // grid to element 0 with a zero ve, where hs[0] would not be zero.
   __device__ inline void rows(int64_t e, int, int, int, int a, const T* ve, T* acc) const {
@@ -784,79 +780,26 @@ __device__ inline void node_apply_fine3(const Op& op, const Dims& d, int i, int 
   }
 }
 
-// Element products of the finest 3D level, y_e = x_e K0 v_e (+ h_e (h_e'v_e) for the
-// augmented system), one thread per element: all 24 rows, every matrix entry a
-// signed copy of one of the 14 cube constants at compile time (no matrix loads),
-// h_e'v_e summed in column order; 32-bit index arithmetic (the grid has < 2^31
-// slots).  Measured faster than 8 waves per 64 elements (one row group each, h_e'v_e
-// combined in LDS) and than the node passes gathering the element rows themselves.
-template <typename T, bool Z>
-__global__ __launch_bounds__(BS) void k_elem_fine3e(Dims d, const T* __restrict__ x, const T* __restrict__ h,
-                                                    const T* __restrict__ v, T* __restrict__ ye, const int* gate) {
+// out = omega D^-1 r on the finest 3D level (first sweep from zero; dgn: the diagonal
+// per slot, 0 on clamped slots).
+template <typename T>
+__global__ __launch_bounds__(BS) void k_fine_jacobi0(const T* __restrict__ dgn, const T* __restrict__ r,
+                                                     T* __restrict__ out, int64_t n, const double* __restrict__ omg,
+                                                     int aug, double c, const int* gate) {
   if (gate && *gate) return;
-  const int e = (int)(blockIdx.x * BS + threadIdx.x);
-  if (e >= (int)d.m) return;
-  const int ei = e % d.nx, t = e / d.nx, ej = t % d.ny, ek = t / d.ny;
-  T ve[24];
-#pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    const int ni = ei + loc_x(b), nj = ej + loc_y(b), nk = ek + loc_z(b);
-    const int qn = ni >= 1 ? (nk * d.ny1 + nj) * d.nx1 + ni : 0;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) ve[b * 3 + c] = v[3 * qn + c];
-  }
-  const int m = (int)d.m;
-  T hh[Z ? 24 : 1];
-  T hv = 0;
-  if constexpr (Z) {
-#pragma unroll
-    for (int col = 0; col < 24; ++col) hh[col] = h[col * m + e];
-#pragma unroll
-    for (int col = 0; col < 24; ++col) hv += hh[col] * ve[col];
-  }
-  const T xe = x[e];
-#pragma unroll
-  for (int r = 0; r < 24; ++r) {
-    T y = 0;
-#pragma unroll
-    for (int col = 0; col < 24; ++col) y += k0cube<T>(r, col) * ve[col];
-    y *= xe;
-    if constexpr (Z) y += hh[r] * hv;
-    ye[r * m + e] = y;
-  }
-}
-
-// Rows (from the element products ye) and diagonal (per slot, dgn) of a node of the
-// finest 3D level.
-template <typename T, bool ROWS, bool DIAG>
-__device__ inline void node_apply_fine_ye3(const T* __restrict__ ye, const T* __restrict__ dgn, int64_t m,
-                                           const Dims& d, int i, int j, int k, T* acc, T* dg) {
-  if constexpr (ROWS) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int ex = q & 1, ey = (q >> 1) & 1, ez = q >> 2;
-      const int ei = i - 1 + ex, ej = j - 1 + ey, ek = k - 1 + ez;
-      const bool ok = ei >= 0 && ei < d.nx && ej >= 0 && ej < d.ny && ek >= 0 && ek < d.nz;
-      const int64_t e = ok ? ((int64_t)ek * d.ny + ej) * d.nx + ei : 0;
-      const int a = loc_index(1 - ex, 1 - ey, 1 - ez);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) acc[c] += ok ? ye[(a * 3 + c) * m + e] : T(0);
-    }
-  }
-  if constexpr (DIAG) {
-    const int64_t q = ((int64_t)k * d.ny1 + j) * d.nx1 + i;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) dg[c] += dgn[3 * q + c];
+  const int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x;
+  const T omega = T(*omg);
+  if (t < n) {
+    const T g = dgn[t];
+    out[t] = g != T(0) ? omega * r[t] * recip(g) : T(0);
+  } else if (t == n && aug) {
+    out[t] = T((double)omega * (double)r[t] / c);
   }
 }
 
 template <typename T, class Op, bool ROWS, bool DIAG>
 __device__ inline void node_apply_gather3(const Op& op, const Dims& d, int i, int j, int k, const T* __restrict__ v,
                                           T* acc, T* dg) {
-  if constexpr (fine3_op<Op>::value) {
-    if ((!ROWS || op.ye) && (!DIAG || op.dgn))
-      return node_apply_fine_ye3<T, ROWS, DIAG>(op.ye, op.dgn, op.m, d, i, j, k, acc, dg);
-  }
   if constexpr (std::is_same<Op, OpFineK<3, T>>::value) {
     return node_apply_fine3<T, Op, ROWS, DIAG>(op, d, i, j, k, v, acc, dg);
   } else if constexpr (std::is_same<Op, OpFineZ<3, T>>::value) {
@@ -903,8 +846,6 @@ __global__ __launch_bounds__(BS) void k_fine_diag3(Op op, Dims d, T* __restrict_
   if (t >= d.nnodes) return;
   const int i = (int)(t % d.nx1), j = (int)((t / d.nx1) % d.ny1), k = (int)(t / ((int64_t)d.nx1 * d.ny1));
   T acc[3] = {T(0), T(0), T(0)}, dg[3] = {T(0), T(0), T(0)};
-  op.ye = nullptr;
-  op.dgn = nullptr;
   if (i > 0) node_apply_fine3<T, Op, false, true>(op, d, i, j, k, nullptr, acc, dg);
 #pragma unroll
   for (int c = 0; c < 3; ++c) dgn[3 * t + c] = dg[c];
@@ -925,8 +866,6 @@ __device__ inline void level_node(const Op& op, const Dims& d, int i, int j, int
     }
     T acc[3] = {T(0), T(0), T(0)}, dg[3] = {T(0), T(0), T(0)}, vc[3] = {T(0), T(0), T(0)};
     if constexpr (MODE != M_JACOBI0) load_node<3, T>(v, q, vc);
-    // no diagonal where the pass has none: a product or a residual then takes its rows
-    // from the element products whether or not the set-up diagonal is at hand
     node_apply_gather3<T, Op, MODE != M_JACOBI0, MODE != M_APPLY && MODE != M_RESID>(op, d, i, j, k, v, acc, dg);
     level_node_finish<3, T, MODE>(q, acc, dg, vc, r, out, omega, augb, vl, pin, dot64, bdot, red0, red1);
   } else {

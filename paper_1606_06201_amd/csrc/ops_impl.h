@@ -10,6 +10,7 @@
 #include "kernels.h"
 #include "fused2d.h"
 #include "stencil.h"
+#include "fine3.h"
 #include "dense.h"
 
 namespace ipmg {
@@ -504,13 +505,14 @@ static __global__ __launch_bounds__(BS) void k_simp_design(int64_t m, const doub
 // Per element: bcoef = c (W w), rcoef = c (W (G3 w)) (coefficients of K0 u_e in the
 // border B^ D^-1 e and in B^ D^-1 G3), the lumped rank-one weight wt = c^2 (W2 w)
 // ((W2)_ji = W_ji^2), the preconditioner's factor h_e = sqrt(wt) g_e (h64, and the
-// V-cycle copy hT), and the partials of its corner sum bcoef^2 / wt.
+// V-cycle copy hT; SWo: sqrt(wt)), and the partials of its corner sum bcoef^2 / wt.
 template <int DIM, typename T>
 __global__ __launch_bounds__(BS) void k_simp_coef(Dims d, const double* __restrict__ cf,
                                                   const double* __restrict__ Ww, const double* __restrict__ WGw,
                                                   const double* __restrict__ W2w, const double* __restrict__ g,
                                                   double* __restrict__ bcoef, double* __restrict__ rcoef,
-                                                  double* __restrict__ h64, T* __restrict__ hT, Red red) {
+                                                  double* __restrict__ SWo, double* __restrict__ h64,
+                                                  T* __restrict__ hT, Red red) {
   constexpr int ND = Geo<DIM>::ND;
   const int64_t e = (int64_t)blockIdx.x * BS + threadIdx.x;
   double acc[1] = {0.0};
@@ -518,6 +520,7 @@ __global__ __launch_bounds__(BS) void k_simp_coef(Dims d, const double* __restri
     const double c = cf[e], bc = c * Ww[e], wt = c * c * W2w[e], sw = sqrt(wt);
     bcoef[e] = bc;
     rcoef[e] = c * WGw[e];
+    SWo[e] = sw;
 #pragma unroll
     for (int rr = 0; rr < ND; ++rr) {
       const double hv = sw * g[rr * d.m + e];
@@ -907,7 +910,12 @@ struct OpsImpl : Ops {
   }
   bool jacobi2(Ctx& c, int lev, int op, const void* r, void* out, const double* omg, const int* gate) override {
     if constexpr (DIM != 2) {
-      return false;
+      if (lev != c.L - 1 || !c.elem_fine3) return false;
+      const Level& l = c.lev[lev];
+      void* z1 = out == l.z ? l.z2 : l.z;             // the buffer that out is not
+      if (c.fp32) fine3_jacobi2<float>(c, op, (const float*)r, (float*)out, (float*)z1, omg, gate);
+      else fine3_jacobi2<double>(c, op, (const double*)r, (double*)out, (double*)z1, omg, gate);
+      return true;
     } else {
       if (op != IPMG_OP_K || !c.fold_prolong || lev != c.L - 1) return false;
       const Dims& d = c.lev[lev].d;
@@ -990,26 +998,88 @@ struct OpsImpl : Ops {
 #undef IPMG_LEVEL_CASE
   }
 
-  // 3D finest level: element products of v into ye (the operator's rows for the
-  // node pass) and the set-up diagonal; false when the element passes are off.
-  template <typename T, class Op>
-  bool fine_elem3(Ctx& c, Op& o, const T* v, T* ye, const T* dgn, const int* gate, int cls) {
-    if constexpr (DIM != 3) {
-      return false;
-    } else {
-      if (!ye) return false;
-      const Dims& d = c.fine();
-      if (v) {
-        constexpr bool Z = std::is_same<Op, OpFineZ<3, T>>::value;
-        const T* h = nullptr;
-        if constexpr (Z) h = o.h;
-        ProfScope ps(c, cls);
-        k_elem_fine3e<T, Z><<<lin_grid(d.m), BS, 0, c.stream>>>(d, o.x, h, v, ye, gate);
-        o.ye = ye;
-      }
-      o.dgn = dgn;
-      return true;
+  // 3D finest level (fine3.h).  A block marches over TZ node planes; one layer of
+  // elements per block is formed twice, so the planes are split only until every CU
+  // has two blocks.
+  struct Fine3Grid {
+    dim3 g;
+    int tz;
+  };
+  Fine3Grid fine3_grid(const Ctx& c, const Dims& d) const {
+    const unsigned gx = (unsigned)((d.nx + F3_TX - 1) / F3_TX), gy = (unsigned)((d.ny1 + F3_TY - 1) / F3_TY);
+    const int chunks = std::max(1, std::min(d.nz1 / 2, (int)((2 * c.cus + gx * gy - 1) / (gx * gy))));
+    const int tz = (d.nz1 + chunks - 1) / chunks;
+    return {dim3(gx, gy, (unsigned)((d.nz1 + tz - 1) / tz)), tz};
+  }
+  template <typename T>
+  Fine3<T> fine3_op(const Ctx& c, int op) const {
+    const double mu = c.desc.E / (2.0 * (1.0 + c.desc.nu));
+    const double lam = c.desc.E * c.desc.nu / ((1.0 + c.desc.nu) * (1.0 - 2.0 * c.desc.nu));
+    Fine3<T> o;
+    o.x = (const T*)(sizeof(T) == 8 ? (const void*)c.x64 : c.xT);
+    o.dgn = (const T*)c.fine_dg;
+    o.u = op == IPMG_OP_Z ? c.hu : nullptr;
+    o.s = op == IPMG_OP_Z ? c.ipSW : nullptr;
+    o.cl = lam / 16.0;
+    o.cm = mu / 16.0;
+    return o;
+  }
+  template <typename T, int MODE>
+  void fine3_mode(Ctx& c, int op, const T* v, const T* r, T* out, const double* omg, Aug<T> aug, int sidx_in,
+                  const int* gate, const double* dot64, T* vlam) {
+    const Dims& d = c.fine();
+    const Fine3Grid f = fine3_grid(c, d);
+    ProfScope ps(c, c.prof_tag);
+    if (op == IPMG_OP_K)
+      k_fine3<T, false, MODE, T><<<f.g, F3_THREADS, 0, c.stream>>>(fine3_op<T>(c, op), d, f.tz, v, r, out, omg, aug,
+                                                                   c.red, sidx_in, dot64, vlam, Dir3<T>{}, gate);
+    else
+      k_fine3<T, true, MODE, T><<<f.g, F3_THREADS, 0, c.stream>>>(fine3_op<T>(c, op), d, f.tz, v, r, out, omg, aug,
+                                                                  c.red, sidx_in, dot64, vlam, Dir3<T>{}, gate);
+  }
+  template <typename T>
+  void launch_fine3(Ctx& c, int op, int mode, const T* v, const T* r, T* out, const double* omg, Aug<T> aug, int sidx,
+                    int sidx_in, const int* gate, const double* dot64) {
+    const Dims& d = c.fine();
+    const dim3 g = fine3_grid(c, d).g;
+    const unsigned nb = g.x * g.y * g.z;
+    IPMG_REQUIRE((int64_t)nb <= MAX_PARTIALS, IPMG_E_INVALID, "grid too large for one reduction");
+    const bool fin = aug.b || mode == M_POWER || mode == M_RAYLEIGH || mode == M_JACOBI_BETA;
+#define IPMG_F3_CASE(M)                                                                                       \
+  case M:                                                                                                     \
+    fine3_mode<T, M>(c, op, v, r, out, omg, aug, sidx_in, gate, dot64, nullptr);                              \
+    if (fin)                                                                                                  \
+      k_level_fin<T, M><<<1, BS, 0, c.stream>>>(v, r, out, omg, aug.b != nullptr, aug.c, aug.n, dot64, c.red, nb, \
+                                                 sidx, sidx_in, gate,                                        \
+                                                 M == M_JACOBI_BETA ? c.take_flag_dst() : nullptr);          \
+    break;
+    switch (mode) {
+      IPMG_F3_CASE(M_APPLY)
+      IPMG_F3_CASE(M_RESID)
+      IPMG_F3_CASE(M_JACOBI)
+      IPMG_F3_CASE(M_POWER)
+      IPMG_F3_CASE(M_RAYLEIGH)
+      IPMG_F3_CASE(M_JACOBI_BETA)
+      default: throw Error(IPMG_E_INVALID, "bad level mode");
     }
+#undef IPMG_F3_CASE
+  }
+  template <typename T>
+  void fine3_jacobi0(Ctx& c, const Dims& d, const T* r, T* out, const double* omg, Aug<T> aug, const int* gate) {
+    ProfScope ps(c, c.prof_tag);
+    k_fine_jacobi0<T><<<lin_grid(d.nslots + 1), BS, 0, c.stream>>>((const T*)c.fine_dg, r, out, d.nslots, omg,
+                                                                   aug.b != nullptr, aug.c, gate);
+  }
+  // The two sweeps from zero in one pass; the first one's lambda entry goes to z1.
+  template <typename T>
+  void fine3_jacobi2(Ctx& c, int op, const T* r, T* out, T* z1, const double* omg, const int* gate) {
+    const Dims& d = c.fine();
+    const Aug<T> aug{op == IPMG_OP_Z ? (const T*)c.lev[c.L - 1].bZ : nullptr, c.cZ, d.nslots};
+    const dim3 g = fine3_grid(c, d).g;
+    fine3_mode<T, M_JACOBI2>(c, op, nullptr, r, out, omg, aug, -1, gate, nullptr, z1);
+    if (aug.b)
+      k_level_fin<T, M_JACOBI><<<1, BS, 0, c.stream>>>(z1, r, out, omg, 1, aug.c, aug.n, nullptr, c.red,
+                                                       g.x * g.y * g.z, 0, -1, gate, nullptr);
   }
 
   // The finest-level augmented operator for a pass over v (null: the pass reads
@@ -1032,22 +1102,22 @@ struct OpsImpl : Ops {
     const Dims& d = c.lev[lev].d;
     Aug<T> aug{op == IPMG_OP_Z ? (const T*)c.lev[lev].bZ : nullptr, c.cZ, d.nslots};
     if (lev == c.L - 1) {
-      // 3D: element products first, the diagonal from set-up (formed before the
-      // damping estimates)
       const T* vv = mode != M_JACOBI0 ? (const T*)v : nullptr;
-      const bool elem = DIM == 3 && c.fine_ye && c.fine_dg;
-      if (op == IPMG_OP_K) {
-        OpFineK<DIM, T> o{(const T*)c.xT, d.m};
-        if (elem) fine_elem3<T>(c, o, vv, (T*)c.fine_ye, (const T*)c.fine_dg, gate, PC_ELEM3);
-        launch_level<T>(c, d, o, mode, (const T*)v, (const T*)r, (T*)out, omg, aug, sidx, sidx_in, gate, dot64);
-      } else if (elem) {
-        OpFineZ<DIM, T> o{(const T*)(sizeof(T) == 8 ? (const void*)c.x64 : c.xT), (const T*)c.hT, d.m};
-        fine_elem3<T>(c, o, vv, (T*)c.fine_ye, (const T*)c.fine_dg, gate, PC_ELEM3);
-        launch_level<T>(c, d, o, mode, (const T*)v, (const T*)r, (T*)out, omg, aug, sidx, sidx_in, gate, dot64);
-      } else {
-        launch_level<T>(c, d, fine_z<T>(c, (const T*)c.hT, vv), mode,
-                        (const T*)v, (const T*)r, (T*)out, omg, aug, sidx, sidx_in, gate, dot64);
+      if constexpr (DIM == 3) {
+        if (c.elem_fine3) {
+          if (mode == M_JACOBI0)
+            fine3_jacobi0<T>(c, d, (const T*)r, (T*)out, omg, aug, gate);
+          else
+            launch_fine3<T>(c, op, mode, vv, (const T*)r, (T*)out, omg, aug, sidx, sidx_in, gate, dot64);
+          return;
+        }
       }
+      if (op == IPMG_OP_K)
+        launch_level<T>(c, d, OpFineK<DIM, T>{(const T*)c.xT, d.m}, mode, (const T*)v, (const T*)r, (T*)out, omg, aug,
+                        sidx, sidx_in, gate, dot64);
+      else
+        launch_level<T>(c, d, fine_z<T>(c, (const T*)c.hT, vv), mode, (const T*)v, (const T*)r, (T*)out, omg, aug, sidx,
+                        sidx_in, gate, dot64);
     } else if (DIM == 2 && op == IPMG_OP_K && lev == c.L - 2 && c.coarse_from_x) {
       launch_level<T>(c, d, OpCoarse2K<DIM, T>{(const T*)c.xT, c.fine().nx, c.fine().m}, mode, (const T*)v, (const T*)r,
                       (T*)out, omg, aug, sidx, sidx_in, gate, dot64);
@@ -1096,13 +1166,21 @@ struct OpsImpl : Ops {
     }
     IPMG_REQUIRE(!zs, IPMG_E_STATE, "solution update folded into an untiled direction kernel");
     if constexpr (DIM == 3) {
-      k_pdir3<TY><<<lin_grid(d.nslots), BS, 0, c.stream>>>(d, y, pold, p, c.red, first, gate);
-      Op o = op;
-      if (!fine_elem3<double>(c, o, p, c.fine_ye64, nullptr, gate, PC_ELEM3_DIR)) {
+      if (c.elem_fine3) {
+        const Fine3Grid f = fine3_grid(c, d);
+        constexpr bool Z = std::is_same<Op, OpFineZ<DIM, double>>::value;
+        g = f.g;
+        ProfScope ps(c, PC_DIR_APPLY);
+        k_fine3<double, Z, F3_DIR, TY><<<g, F3_THREADS, 0, c.stream>>>(
+            fine3_op<double>(c, Z ? IPMG_OP_Z : IPMG_OP_K), d, f.tz, nullptr, nullptr, q, nullptr, aug, c.red, -1,
+            nullptr, nullptr, Dir3<TY>{y, pold, p, first}, gate);
+      } else {
+        k_pdir3<TY><<<lin_grid(d.nslots), BS, 0, c.stream>>>(d, y, pold, p, c.red, first, gate);
+        Op o = op;
         if constexpr (std::is_same<Op, OpFineZ<DIM, double>>::value) o = fine_z<double>(c, c.h64, p);   // h_e'p_e
+        ProfScope ps(c, PC_DIR_APPLY);
+        k_dir_apply3<TY, Op><<<g, BS, 0, c.stream>>>(o, d, y, pold, p, q, aug, c.red, first, gate);
       }
-      ProfScope ps(c, PC_DIR_APPLY);
-      k_dir_apply3<TY, Op><<<g, BS, 0, c.stream>>>(o, d, y, pold, p, q, aug, c.red, first, gate);
     } else {
       ProfScope ps(c, PC_DIR_APPLY);
       k_dir_apply<DIM, TY, Op><<<g, BS, 0, c.stream>>>(op, d, y, pold, p, q, aug, c.red, first, gate);
@@ -1135,15 +1213,22 @@ struct OpsImpl : Ops {
 
   void fine_apply64(Ctx& c, int op, const double* v, double* y, const int* gate) override {
     const Dims& d = c.fine();
+    if constexpr (DIM == 3) {
+      if (c.elem_fine3) {
+        const int tag = c.prof_tag;
+        c.prof_tag = -1;
+        launch_fine3<double>(c, op, M_APPLY, v, nullptr, y, nullptr,
+                             Aug<double>{op == IPMG_OP_Z ? c.bZ64 : nullptr, c.cZ, d.nslots}, 0, -1, gate, nullptr);
+        c.prof_tag = tag;
+        return;
+      }
+    }
     if (op == IPMG_OP_K) {
       OpFineK<DIM, double> o{c.x64, d.m};
-      fine_elem3<double>(c, o, v, c.fine_ye64, nullptr, gate, -1);
       launch_level<double>(c, d, o, M_APPLY, v, nullptr, y, nullptr, Aug<double>{nullptr, 0.0, d.nslots}, 0, -1,
                            gate);
     } else {
-      OpFineZ<DIM, double> o{c.x64, c.h64, d.m};
-      if (!fine_elem3<double>(c, o, v, c.fine_ye64, nullptr, gate, -1)) o = fine_z<double>(c, c.h64, v);
-      launch_level<double>(c, d, o, M_APPLY, v, nullptr, y, nullptr, Aug<double>{c.bZ64, c.cZ, d.nslots}, 0, -1,
+      launch_level<double>(c, d, fine_z<double>(c, c.h64, v), M_APPLY, v, nullptr, y, nullptr, Aug<double>{c.bZ64, c.cZ, d.nslots}, 0, -1,
                            gate);
     }
   }
@@ -1767,11 +1852,11 @@ struct OpsImpl : Ops {
                  double* bcoef, double* rcoef) override {
     const Dims& d = c.fine();
     if (c.fp32)
-      k_simp_coef<DIM, float><<<lin_grid(d.m), BS, 0, c.stream>>>(d, cf, Ww, WGw, W2w, g, bcoef, rcoef, c.h64,
-                                                                  (float*)c.hT, c.red);
+      k_simp_coef<DIM, float><<<lin_grid(d.m), BS, 0, c.stream>>>(d, cf, Ww, WGw, W2w, g, bcoef, rcoef, c.ipSW,
+                                                                  c.h64, (float*)c.hT, c.red);
     else
-      k_simp_coef<DIM, double><<<lin_grid(d.m), BS, 0, c.stream>>>(d, cf, Ww, WGw, W2w, g, bcoef, rcoef, c.h64,
-                                                                   nullptr, c.red);
+      k_simp_coef<DIM, double><<<lin_grid(d.m), BS, 0, c.stream>>>(d, cf, Ww, WGw, W2w, g, bcoef, rcoef, c.ipSW,
+                                                                   c.h64, nullptr, c.red);
     k_simp_coef_fin<<<1, BS, 0, c.stream>>>(c.red, lin_grid(d.m));
   }
   void simp_nodes(Ctx& c, const double* Ku, const double* f, const double* u, const double* g, const double* bcoef,

@@ -93,6 +93,7 @@ static void ensure_z_buffers(Ctx& c) {
     if (c.fp32) dalloc(c, c.lev[k].bZ, sizeof(float) * nk);
     else c.lev[k].bZ = c.lev[k].bZ64;
   }
+  if (c.dim == 3) dalloc(c, c.hu, sizeof(double) * n1);
   dalloc(c, c.ipG3, sizeof(double) * m);
   dalloc(c, c.ipW, sizeof(double) * m);
   dalloc(c, c.ipSW, sizeof(double) * m);
@@ -225,9 +226,6 @@ void ctx_init(Ctx& c, const ipmg_desc& d, hipStream_t st) {
   dalloc(c, c.omega_dev, sizeof(double) * 2 * c.L);
   dalloc(c, c.oc_cand, sizeof(double) * OC_CAND);
   if (d.dim == 3 && c.elem_fine3) {
-    dalloc(c, c.fine_ye64, sizeof(double) * 24 * (size_t)fd.m);
-    if (c.fp32) dalloc(c, c.fine_ye, sizeof(float) * 24 * (size_t)fd.m);
-    else c.fine_ye = c.fine_ye64;
     dalloc(c, c.fine_dg, c.tsz * (size_t)fd.nslots);
   }
   vfill_small(st, c.omega_dev, c.L, d.omega);
@@ -353,7 +351,8 @@ void mg_setup(Ctx& c, int op, double* ms) {
 // beta64 (finest level only): if not null, the last post-smoothing sweep also
 // forms beta = beta64'y / rho of Algorithm PCG on the device.
 // A ||r||^2 finalize left pending by pcg_iteration (c.rn2_fin_blocks) is done by
-// the finest level's fused first two sweeps, else here before the first kernel.
+// the finest 2D level's fused first two sweeps, else here before the first kernel
+// (whose partials take the same place).
 static void rn2_fin_flush(Ctx& c, const int* gate) {
   if (!c.rn2_fin_blocks) return;
   vpcg_update_fin_nb(c.stream, c.rn2_fin_blocks, c.red, gate, c.rn2_fin_zpend);
@@ -426,7 +425,7 @@ static void* vcycle_level(Ctx& c, int op, int k, const int* gate, const double* 
     return l.z;
   }
   if (c.ops->sten_level(c, k, op)) return vcycle_sten(c, op, k, gate, beta64);
-  if (c.rn2_fin_blocks && (k == 0 || c.ops->fused_applies(c, k, op) || c.desc.nu_pre < 2)) rn2_fin_flush(c, gate);
+  if (c.rn2_fin_blocks && (k == 0 || c.ops->fused_applies(c, k, op) || c.desc.nu_pre < 2 || c.dim == 3)) rn2_fin_flush(c, gate);
   if (k == 0) {
     const int n = l.d.nslots + aug;
     if (c.fp32) dense_apply<float, float>(c.stream, c.dAif, c.dpart, n, (const float*)l.r, (float*)l.z, gate);
@@ -833,6 +832,7 @@ static void simp_prepare(Ctx& c, const double* f, const ipmg_ip_params& p, doubl
   c.ipV = p.V;
   simp_densities(c, st.x, rmin, pexp);
   IPMG_HIP(hipMemsetAsync(c.red.flags + F_BAD, 0, sizeof(int), c.stream));
+  if (c.hu) vmask_copy(c.stream, st.u, c.hu, d.nslots, d.nslots, c.dim, d.nx1, c.red, S_QY);
   c.ops->simp_elem(c, st.u, c.simp_g, c.simp_E);
   vmul(c.stream, c.simp_cf, c.simp_E, c.simp_a, d.m);
   c.ops->filter(c, rmin, c.simp_a, c.simp_t, 1);                         // W'(c o E)
@@ -1046,6 +1046,7 @@ void ip_prepare(Ctx& c, const double* f, const ipmg_ip_params& p, const ipmg_ip_
   set_density(c, st.x);
   c.ipV = p.V;
   IPMG_HIP(hipMemsetAsync(c.red.flags + F_BAD, 0, sizeof(int), c.stream));
+  if (c.hu) vmask_copy(c.stream, st.u, c.hu, c.fine().nslots, c.fine().nslots, c.dim, c.fine().nx1, c.red, S_QY);
   c.ops->ip_elements(c, st.u, st.x, st.phi, st.psi, st.lam, st.s, st.r, p.xbar);
   c.ops->fine_apply64(c, IPMG_OP_K, st.u, c.ipKu, nullptr);
   c.ops->ip_nodes(c, c.ipKu, f, st.u, c.ipRhs);
