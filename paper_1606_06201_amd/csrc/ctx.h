@@ -118,6 +118,7 @@ struct Ops {
   //   level of the one-workgroup V-cycle (0: none); needs_elements: the level's
   //   passes read the element matrices in V-cycle precision.
   virtual bool sten_level(const Ctx& c, int lev, int op) const = 0;
+  virtual bool pow_level(const Ctx& c, int lev, int op) const = 0;   // damping estimated on the stencil
   virtual int tail_level(const Ctx& c, int op) const = 0;
   virtual bool needs_elements(const Ctx& c, int lev, int op) const = 0;
   // Stencils and the damping of every level above.
@@ -191,7 +192,7 @@ struct Ctx {
   size_t tsz = 4;              // sizeof(T) of the V-cycle
   bool coarse_from_x = true;   // 2D K: first coarse level evaluated from the fine densities
   bool tiled2d = true;         // 2D level passes with register-blocked tiles
-  int64_t tiled_min_nodes = (int64_t)1 << 18;  // ... on levels with at least this many nodes
+  int64_t tiled_min_nodes = (int64_t)1 << 17;  // ... on levels with at least this many nodes
   int nj32 = 4, nj64 = 2, nj_dir = 4;          // nodes per thread of the tiled passes
   bool fused2d = true;         // 2D K coarse levels: two fused launches per level
   bool fused_staged = true;    // ... with the element matrices staged in LDS (FP32 stored levels
@@ -206,6 +207,7 @@ struct Ctx {
   bool fold_restrict = true;         // finest residual restricted inside the first coarse down pass
   const void* down_from_t = nullptr; // ... the residual, pending for that pass
   bool tail_on = true;         // small levels' V-cycle in one workgroup
+  bool sten2d = true;          // 2D levels on node stencils
   bool step_in_tail = false;   // the tail ends the PCG step (finest level in the tail) ...
   unsigned step_blocks = 0;    // ... whose direction kernel left this many blocks' partials
   int step_first = 0;

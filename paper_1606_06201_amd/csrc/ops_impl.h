@@ -1275,6 +1275,8 @@ struct OpsImpl : Ops {
   // is 5 us a pass, what a launch costs) and their vectors fit in its LDS; the
   // finest level only below the register-blocked sizes.
   static constexpr int64_t TAIL_BYTES = 320 * 1024;
+  // Largest 2D level on its stencil: at 2^18 nodes it is 38 MB in FP32, 75 MB in FP64.
+  static constexpr int64_t STEN_MAX_NODES = (int64_t)1 << 18;
   // LDS entries of a level's vectors: r, pad, a, pad, b, pad (level 0: r, z, pad); a
   // pad holds the neighbours that an index past either end of the grid can reach.
   static int64_t tail_pad(const Dims& d) {
@@ -1300,7 +1302,18 @@ struct OpsImpl : Ops {
     if (lev < 1) return false;
     if (lev <= tail_level(c, op)) return true;
     if (DIM == 3) return lev < c.L - 1;
-    return op == IPMG_OP_Z && c.lev[lev].d.nnodes < c.tiled_min_nodes;
+    // 2D: the augmented system, and K in FP64, below the register-blocked sizes (one
+    // launch a sweep and two for the first pair; FP64 K before: 3.5 us passes that form
+    // the element rows, 5.4 us on the first coarse level, fused pairs of 12.6 + 10.7 us)
+    if (!c.sten2d) return false;
+    return op == IPMG_OP_Z ? c.lev[lev].d.nnodes < STEN_MAX_NODES
+                           : !c.fp32 && c.lev[lev].d.nnodes < c.tiled_min_nodes;
+  }
+  // Levels whose damping is estimated on the stencil, all in one launch per power step;
+  // for K in FP32 that is all their stencil is used for.
+  bool pow_level(const Ctx& c, int lev, int op) const override {
+    return sten_level(c, lev, op) ||
+           (DIM == 2 && lev >= 1 && c.sten2d && c.lev[lev].d.nnodes < STEN_MAX_NODES);
   }
   bool needs_elements(const Ctx& c, int lev, int op) const override {
     return DIM == 2 && lev >= 1 && lev < c.L - 1 && !sten_level(c, lev, op);
@@ -1318,7 +1331,7 @@ struct OpsImpl : Ops {
   template <typename T>
   void sten_setup_t(Ctx& c, int op) {
     for (int k = 1; k < c.L; ++k) {
-      if (!sten_level(c, k, op)) continue;
+      if (!pow_level(c, k, op)) continue;
       Level& l = c.lev[k];
       const Dims& d = l.d;
       if (!l.S) {
@@ -1429,7 +1442,7 @@ struct OpsImpl : Ops {
     PowArgs<T> A{};
     unsigned nblk = 0;
     for (int k = top + 1; k < c.L; ++k) {
-      if (!sten_level(c, k, op)) continue;
+      if (!pow_level(c, k, op)) continue;
       Level& l = c.lev[k];
       IPMG_REQUIRE(A.nlev < POW_LEVELS, IPMG_E_STATE, "too many levels in the damping estimate");
       PowLevel<T>& p = A.lv[A.nlev++];
@@ -1577,7 +1590,7 @@ struct OpsImpl : Ops {
       // faster).  The first coarse level formed from the densities is VALU-bound:
       // fused (with its recomputed halos) it pays in FP32 only.
       const bool from_x = lev == c.L - 2 && c.coarse_from_x;
-      return c.fused2d && lev > tail_level(c, op) && op == IPMG_OP_K && c.desc.nu_pre == 2 && c.desc.nu_post == 2 && lev >= 1 &&
+      return c.fused2d && !sten_level(c, lev, op) && op == IPMG_OP_K && c.desc.nu_pre == 2 && c.desc.nu_post == 2 && lev >= 1 &&
              lev < c.L - 1 && (!from_x || c.fp32);
     }
   }

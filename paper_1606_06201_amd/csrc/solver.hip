@@ -161,7 +161,7 @@ void ctx_init(Ctx& c, const ipmg_desc& d, hipStream_t st) {
   for (const char* v : {"IPMG_STORED_COARSE", "IPMG_UNTILED", "IPMG_UNFUSED", "IPMG_UNSTAGED",
                         "IPMG_STAGED_MAX_NODES", "IPMG_TILED_MIN_NODES", "IPMG_NO_MFMA", "IPMG_NO_FOLD_RESTRICT", "IPMG_NO_ELEM_FINE3",
                         "IPMG_NO_ELEM_HV"})
-    if (std::getenv(v)) c.tail_on = false;
+    if (std::getenv(v)) c.tail_on = c.sten2d = false;
   c.power_steps = POWER_STEPS;
   c.power_steps_z = POWER_STEPS_Z;
   if (const char* e = std::getenv("IPMG_TILED_MIN_NODES")) c.tiled_min_nodes = std::max<int64_t>(0, std::atoll(e));
@@ -294,7 +294,7 @@ static void jacobi_damping(Ctx& c, int k, int op, int steps, double product) {
 static void damping_all(Ctx& c, int op, int steps, double product) {
   c.ops->sten_damping(c, op, steps, product);
   for (int k = 1; k < c.L; ++k)
-    if (!c.ops->sten_level(c, k, op)) jacobi_damping(c, k, op, steps, product);
+    if (!c.ops->pow_level(c, k, op)) jacobi_damping(c, k, op, steps, product);
 }
 
 static void ensure_dense(Ctx& c) {

@@ -114,8 +114,8 @@ __device__ inline double wave_sum_dpp(double v) {
 // One pass over a level.  A block takes 64 nodes; in 3D wave (c, dz) sums row c
 // over the neighbours of plane dz (27 coefficients and 27 values a thread, all
 // loads in flight) and the first three waves add the planes; in 2D wave c takes
-// row c (18 of each).  part: partial slots of this pass (b'v; dot64'out),
-// MAX_PARTIALS apart.  lam_out: receives the lambda entry of v (LAM_SWEEP kinds).
+// row c (18 of each).  part: partial slots of this pass (b'v, then dot64'out;
+// without a border dot64'out), MAX_PARTIALS apart.  lam_out: receives the lambda entry of v (LAM_SWEEP kinds).
 template <int DIM, typename T, int MODE>
 __global__ __launch_bounds__(64 * Sten<DIM>::WAVES) void k_sten(StenLevel<T> L, const T* __restrict__ v,
                                                                 const T* __restrict__ r, T* __restrict__ out,
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(64 * Sten<DIM>::WAVES) void k_sten(StenLevel<T> L, 
       a += shr[0][u];
       b += shr[1][u];
     }
-    part[tile] = a;
+    part[tile] = MODE == ST_BETA && !border ? b : a;       // the first slot, without a border
     if constexpr (MODE == ST_BETA) part[MAX_PARTIALS + tile] = b;
   }
 }
