@@ -88,7 +88,8 @@ enum Scal {
 // F_ZPEND: the solution update z += alpha p of the last PCG step is pending (it
 // is folded into the next step's direction kernel).
 // F_OCDONE: the bisection of the OC update has narrowed its bracket to tau.
-enum Flag { F_DONE = 0, F_ITERS, F_STATUS, F_BAD, F_ZPEND, F_OCDONE, F_COUNT = 8 };
+// F_XBAD: a density is not positive and finite.
+enum Flag { F_DONE = 0, F_ITERS, F_STATUS, F_BAD, F_ZPEND, F_OCDONE, F_XBAD, F_COUNT = 8 };
 // Trial multipliers of one bisection pass: the midpoints of the next OC_LEVELS
 // levels of the bisection tree.
 constexpr int OC_LEVELS = 5;
@@ -104,6 +105,22 @@ struct Red {
   unsigned* counter;  // C_COUNT
   double* scal;       // S_COUNT
   int* flags;         // F_COUNT
+};
+
+// What the host reads, in pinned memory that the GPU writes directly: the scalars and
+// flags (publish), and the stop flag of the PCG steps in flight (two slots), each
+// with the sequence number that the host waits for.
+struct HostBox {
+  double scal[S_COUNT];
+  double extra;                  // one more value asked for with the scalars
+  int flags[F_COUNT];
+  unsigned long long seq;
+  unsigned long long slot[2];    // sequence number << 32 | flags[F_DONE]
+};
+// Where the last kernel of a PCG step puts the stop flag (null: nowhere).
+struct FlagDst {
+  unsigned long long* p = nullptr;
+  unsigned seq = 0;
 };
 
 // Scalar type of the V-cycle.

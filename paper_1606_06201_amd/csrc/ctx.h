@@ -254,16 +254,19 @@ struct Ctx {
 
   // reductions / scalars
   Red red{};
-  double* hscal = nullptr;     // pinned host mirror of scal
-  int* hflags = nullptr;       // pinned host mirror of flags
-  // Within a PCG iteration: the pinned host slot that the iteration's last kernel
-  // (the finalize of the fused PCG ratio) fills with the flags, and whether one did.
-  int* flag_dst = nullptr;
+  HostBox* box = nullptr;      // pinned host memory that kernels write ...
+  double* hscal = nullptr;     // ... its scalars
+  int* hflags = nullptr;       // ... and flags
+  unsigned long long box_seq = 0;
+  unsigned step_seq = 0;
+  // Within a PCG iteration: the host slot that the iteration's last kernel (the
+  // finalize of the fused PCG ratio) fills, and whether one did.
+  FlagDst flag_dst;
   bool flag_written = false;
-  int* take_flag_dst() {
-    int* p = flag_dst;
-    if (p) flag_written = true;
-    flag_dst = nullptr;
+  FlagDst take_flag_dst() {
+    const FlagDst p = flag_dst;
+    if (p.p) flag_written = true;
+    flag_dst = FlagDst{};
     return p;
   }
 
@@ -272,7 +275,6 @@ struct Ctx {
   double *ipRhs = nullptr, *ipD = nullptr, *ipKu = nullptr;
   double ipV = 0.0;            // volume of the current interior-point problem
 
-  hipEvent_t ev0 = nullptr, ev1 = nullptr;
   std::string err;
 
   // 3D finest level: the set-up diagonal; for Z the displacements (0 on clamped
@@ -383,7 +385,9 @@ int pcg(Ctx& c, int op, const double* b, double* u, double rtol, int maxit, ipmg
 int pcg_noalloc(Ctx& c, int op, const double* b, double* u, double rtol, int maxit, ipmg_pcg_info* info);
 size_t pcg_noalloc_bytes(const Ctx& c);
 void sync(Ctx& c);
-void read_scalars(Ctx& c);
+// Scalars and flags (and *extra) of the stream's work so far into hscal, hflags and
+// box->extra; waits for them.
+void read_scalars(Ctx& c, const double* extra = nullptr);
 int ip_init(Ctx& c, const double* f, const ipmg_ip_params& p, ipmg_ip_state& st, ipmg_pcg_info* info);
 void ip_prepare(Ctx& c, const double* f, const ipmg_ip_params& p, const ipmg_ip_state& st);
 int ip_step(Ctx& c, const double* f, const ipmg_ip_params& p, ipmg_ip_state& st, ipmg_ip_info* info);

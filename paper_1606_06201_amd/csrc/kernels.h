@@ -951,23 +951,22 @@ __global__ __launch_bounds__(BS) void k_level(Op op, Dims d, const T* __restrict
 
 // Finalize of a level pass that reduces (augmented border, M_POWER, M_RAYLEIGH,
 // M_JACOBI_BETA): one block of BS threads, launched right after k_level.
-// The device flags into pinned host memory (thread 0): the last kernel of a PCG
-// iteration hands the host its stop test this way instead of a separate copy.
-__device__ inline void flags_to_host(const Red& red, int* __restrict__ h) {
-#pragma unroll
-  for (int f = 0; f < F_COUNT; ++f) h[f] = red.flags[f];
-  __threadfence_system();
+// The stop flag into pinned host memory (one thread): the last kernel of a PCG
+// iteration hands the host its stop test in one store, with the step's number.
+__device__ inline void flags_to_host(const Red& red, const FlagDst& h) {
+  __hip_atomic_store(h.p, ((unsigned long long)h.seq << 32) | (unsigned)red.flags[F_DONE], __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// hflags (M_JACOBI_BETA, may be null): pinned host slot that receives the flags.
+// hflags (M_JACOBI_BETA, may be empty): host slot that receives the stop flag.
 template <typename T, int MODE>
 __global__ __launch_bounds__(BS) void k_level_fin(const T* __restrict__ v, const T* __restrict__ r,
                                                   T* __restrict__ out, const double* __restrict__ omg, int aug,
                                                   double c, int64_t n, const double* __restrict__ dot64, Red red,
                                                   unsigned nblocks, int sidx, int sidx_in, const int* gate,
-                                                  int* hflags) {
+                                                  FlagDst hflags) {
   if (gate && *gate) {
-    if (hflags && threadIdx.x == 0) flags_to_host(red, hflags);
+    if (hflags.p && threadIdx.x == 0) flags_to_host(red, hflags);
     return;
   }
   double tot[3];
@@ -990,7 +989,7 @@ __global__ __launch_bounds__(BS) void k_level_fin(const T* __restrict__ v, const
       if constexpr (MODE == M_RAYLEIGH) red.scal[sidx + 1] = tot[1];
     }
   }
-  if (hflags) flags_to_host(red, hflags);
+  if (hflags.p) flags_to_host(red, hflags);
 }
 
 // Lane-shared register tiles.  The 64 lanes of a wave hold 64 consecutive node

@@ -784,7 +784,7 @@ struct OpsImpl : Ops {
     if (fin)                                                                                                 \
       k_level_fin<T, M><<<1, BS, 0, c.stream>>>(v, r, out, omg, aug.b != nullptr, aug.c, aug.n, dot64, c.red, nb2, \
                                                  sidx, sidx_in, gate,                                       \
-                                                 M == M_JACOBI_BETA ? c.take_flag_dst() : nullptr);         \
+                                                 M == M_JACOBI_BETA ? c.take_flag_dst() : FlagDst{});         \
     return;
     switch (mode) {
       IPMG_L2D_CASE(M_APPLY)
@@ -983,7 +983,7 @@ struct OpsImpl : Ops {
     if (fin)                                                                                                 \
       k_level_fin<T, M><<<1, BS, 0, c.stream>>>(v, r, out, omg, aug.b != nullptr, aug.c, aug.n, dot64, c.red, nb, \
                                                  sidx, sidx_in, gate,                                       \
-                                                 M == M_JACOBI_BETA ? c.take_flag_dst() : nullptr);         \
+                                                 M == M_JACOBI_BETA ? c.take_flag_dst() : FlagDst{});         \
     break;
     switch (mode) {
       IPMG_LEVEL_CASE(M_APPLY)
@@ -1051,7 +1051,7 @@ struct OpsImpl : Ops {
     if (fin)                                                                                                  \
       k_level_fin<T, M><<<1, BS, 0, c.stream>>>(v, r, out, omg, aug.b != nullptr, aug.c, aug.n, dot64, c.red, nb, \
                                                  sidx, sidx_in, gate,                                        \
-                                                 M == M_JACOBI_BETA ? c.take_flag_dst() : nullptr);          \
+                                                 M == M_JACOBI_BETA ? c.take_flag_dst() : FlagDst{});          \
     break;
     switch (mode) {
       IPMG_F3_CASE(M_APPLY)
@@ -1079,7 +1079,7 @@ struct OpsImpl : Ops {
     fine3_mode<T, M_JACOBI2>(c, op, nullptr, r, out, omg, aug, -1, gate, nullptr, z1);
     if (aug.b)
       k_level_fin<T, M_JACOBI><<<1, BS, 0, c.stream>>>(z1, r, out, omg, 1, aug.c, aug.n, nullptr, c.red,
-                                                       g.x * g.y * g.z, 0, -1, gate, nullptr);
+                                                       g.x * g.y * g.z, 0, -1, gate, FlagDst{});
   }
 
   // The finest-level augmented operator for a pass over v (null: the pass reads
@@ -1413,7 +1413,7 @@ struct OpsImpl : Ops {
       A.ld = dense_tiles(n0) * DT;
       A.down = A.up = 1;
       A.dot64 = beta64;
-      A.hflags = beta64 ? c.take_flag_dst() : nullptr;
+      A.hflags = beta64 ? c.take_flag_dst() : FlagDst{};
       k_tail<DIM, T><<<1, NT, 0, c.stream>>>(A, c.red, gate);
       return;
     }
@@ -1425,7 +1425,7 @@ struct OpsImpl : Ops {
     A.up = 1;
     A.pcg.nblk = 0;
     A.dot64 = beta64;
-    A.hflags = beta64 ? c.take_flag_dst() : nullptr;
+    A.hflags = beta64 ? c.take_flag_dst() : FlagDst{};
     k_tail<DIM, T><<<1, NT, 0, c.stream>>>(A, c.red, gate);
   }
   void tail(Ctx& c, int op, const int* gate, const double* beta64) override {

@@ -69,10 +69,34 @@ unsigned char* scratch_address() {
 
 void sync(Ctx& c) { IPMG_HIP(hipStreamSynchronize(c.stream)); }
 
-void read_scalars(Ctx& c) {
-  IPMG_HIP(hipMemcpyAsync(c.hscal, c.red.scal, sizeof(double) * S_COUNT, hipMemcpyDeviceToHost, c.stream));
-  IPMG_HIP(hipMemcpyAsync(c.hflags, c.red.flags, sizeof(int) * F_COUNT, hipMemcpyDeviceToHost, c.stream));
-  sync(c);
+// Waits until `there` holds, which a kernel on the stream brings about.  The host
+// polls (a stream synchronisation or an event costs 10 to 20 us more than the store
+// takes to arrive) and looks at the stream now and then, so that work that ended
+// without the store, or an error, ends the wait.
+template <class F>
+static void wait_for(Ctx& c, F&& there) {
+  for (;;) {
+    for (int spin = 0; spin < 4096; ++spin) {
+      if (there()) return;
+      __builtin_ia32_pause();
+    }
+    const hipError_t e = hipStreamQuery(c.stream);
+    if (e == hipErrorNotReady) {
+      (void)hipGetLastError();                        // not an error to be found later
+      continue;
+    }
+    IPMG_HIP(e);
+    IPMG_REQUIRE(there(), IPMG_E_HIP, "the stream ended without its result");
+    return;
+  }
+}
+static unsigned long long host_load(const unsigned long long* p) { return __atomic_load_n(p, __ATOMIC_ACQUIRE); }
+
+void read_scalars(Ctx& c, const double* extra) {
+  const unsigned long long seq = ++c.box_seq;
+  vpublish(c.stream, c.red, extra, c.box, seq);
+  IPMG_HIP(hipGetLastError());
+  wait_for(c, [&] { return host_load(&c.box->seq) == seq; });
 }
 
 static void ensure_z_buffers(Ctx& c) {
@@ -175,13 +199,12 @@ void ctx_init(Ctx& c, const ipmg_desc& d, hipStream_t st) {
   IPMG_HIP(hipMemsetAsync(c.red.counter, 0, sizeof(unsigned) * C_COUNT, st));
   IPMG_HIP(hipMemsetAsync(c.red.scal, 0, sizeof(double) * S_COUNT, st));
   IPMG_HIP(hipMemsetAsync(c.red.flags, 0, sizeof(int) * F_COUNT, st));
-  if (hipHostMalloc((void**)&c.hscal, sizeof(double) * S_COUNT, hipHostMallocDefault) != hipSuccess)
+  // coherent: kernels write it directly
+  if (hipHostMalloc((void**)&c.box, sizeof(HostBox), hipHostMallocCoherent) != hipSuccess)
     throw Error(IPMG_E_NOMEM, "pinned allocation failed");
-  // coherent: kernels write PCG flags into it directly
-  if (hipHostMalloc((void**)&c.hflags, sizeof(int) * F_COUNT * 4, hipHostMallocCoherent) != hipSuccess)
-    throw Error(IPMG_E_NOMEM, "pinned allocation failed");
-  IPMG_HIP(hipEventCreate(&c.ev0));
-  IPMG_HIP(hipEventCreate(&c.ev1));
+  std::memset(c.box, 0, sizeof(HostBox));
+  c.hscal = c.box->scal;
+  c.hflags = c.box->flags;
   c.noalloc_scratch = scratch_address();
 
   // level vectors
@@ -243,31 +266,32 @@ void ctx_init(Ctx& c, const ipmg_desc& d, hipStream_t st) {
 void ctx_free(Ctx& c) {
   if (c.stream) (void)hipStreamSynchronize(c.stream);
   c.arena.release();
-  if (c.hscal) (void)hipHostFree(c.hscal);
-  if (c.hflags) (void)hipHostFree(c.hflags);
-  c.hscal = nullptr; c.hflags = nullptr;
+  if (c.box) (void)hipHostFree(c.box);
+  c.box = nullptr; c.hscal = nullptr; c.hflags = nullptr;
   for (auto e : c.prof_ev) (void)hipEventDestroy(e);
   c.prof_ev.clear();
   c.prof_cls.clear();
-  if (c.ev0) (void)hipEventDestroy(c.ev0);
-  if (c.ev1) (void)hipEventDestroy(c.ev1);
-  c.ev0 = c.ev1 = nullptr;
   delete c.ops;
   c.ops = nullptr;
 }
 
-void set_density(Ctx& c, const double* x) {
-  const Dims& d = c.fine();
-  IPMG_HIP(hipMemsetAsync(c.red.flags + F_BAD, 0, sizeof(int), c.stream));
-  vcopy_positive(c.stream, x, c.x64, d.m, c.red);
-  if (c.fp32) vconvert<float, double>(c.stream, c.x64, (float*)c.xT, d.m, nullptr);
-  read_scalars(c);
-  if (c.hflags[F_BAD]) {
-    c.have_x = false;
-    throw Error(IPMG_E_DOMAIN, "densities must be finite and positive");
-  }
-  c.have_x = true;
+// x into the context; the flags are cleared first, and F_BAD and F_XBAD set again if
+// a density is not positive and finite.  check_density, after they were read: such a
+// context has no densities.
+static void load_density(Ctx& c, const double* x) {
+  IPMG_HIP(hipMemsetAsync(c.red.flags, 0, sizeof(int) * F_COUNT, c.stream));
+  vcopy_positive(c.stream, x, c.x64, c.fp32 ? (float*)c.xT : nullptr, c.fine().m, c.red);
+}
+static void check_density(Ctx& c) {
+  c.have_x = !c.hflags[F_XBAD];
+  IPMG_REQUIRE(c.have_x, IPMG_E_DOMAIN, "densities must be finite and positive");
   c.hier_op = -1;
+}
+
+void set_density(Ctx& c, const double* x) {
+  load_density(c, x);
+  read_scalars(c);
+  check_density(c);
 }
 
 // Damping of level k from the spectral-radius estimate of D^-1 A (power iteration
@@ -595,8 +619,10 @@ int pcg(Ctx& c, int op, const double* b, double* u, double rtol, int maxit, ipmg
   const int64_t n = d.nslots + (op == IPMG_OP_Z ? 1 : 0);
   const int* gate = c.red.flags + F_DONE;
   IPMG_HIP(hipMemsetAsync(c.red.flags, 0, sizeof(int) * F_COUNT, c.stream));
-  vmask_copy(c.stream, b, c.pb, n, d.nslots, c.dim, d.nx1, c.red, S_BN2);
-  vmask_copy(c.stream, u, c.pu, n, d.nslots, c.dim, d.nx1, c.red, S_TMP1);
+  vpcg_load(c.stream, b, u, c.pb, c.pu, n, d.nslots, c.dim, d.nx1, c.red, rtol, c.desc.pcg_flexible ? 1.0 : 0.0);
+  // r = A u - b
+  c.ops->fine_apply64(c, op, c.pu, c.pq, nullptr);
+  vsub_norm(c.stream, c.pq, c.pb, c.pr, n, c.red, S_RN2);
   read_scalars(c);
   IPMG_REQUIRE(!c.hflags[F_BAD], IPMG_E_DOMAIN, "right-hand side or initial guess is not finite");
   const double bn2 = c.hscal[S_BN2];
@@ -608,40 +634,41 @@ int pcg(Ctx& c, int op, const double* b, double* u, double rtol, int maxit, ipmg
     if (info) *info = inf;
     return IPMG_OK;
   }
-  // r = A u - b
-  c.ops->fine_apply64(c, op, c.pu, c.pq, nullptr);
-  vsub_norm(c.stream, c.pq, c.pb, c.pr, n, c.red, S_RN2);
-  vset_tol(c.stream, c.red, rtol);
-  vfill_small(c.stream, c.red.scal + S_FLEX, 1, c.desc.pcg_flexible ? 1.0 : 0.0);
-  read_scalars(c);
+  // The residual of the iterate, b'u and the iterate itself, all of it read back at
+  // once: the confirmation of a stop is also what the call returns.
+  auto confirm = [&] {
+    c.ops->fine_apply64(c, op, c.pu, c.pq, nullptr);
+    vsub_norm(c.stream, c.pq, c.pb, c.pt, n, c.red, S_TMP2);
+    vdot(c.stream, c.pb, c.pu, n, c.red, S_TMP3, nullptr);
+    IPMG_HIP(hipMemcpyAsync(u, c.pu, sizeof(double) * n, hipMemcpyDeviceToDevice, c.stream));
+    read_scalars(c);
+  };
   int status = IPMG_OK;
   int restarts = 0;
-  double rn2 = c.hscal[S_RN2];
-  bool converged = rn2 <= c.hscal[S_TOL2];
+  bool converged = c.hscal[S_RN2] <= c.hscal[S_TOL2];
   if (!converged) pcg_restart_direction(c, op, n);
-  int enq = 0;   // iterations enqueued in this pass
+  else confirm();
   while (!converged) {
-    // pipeline: keep one iteration in flight while reading the previous flags
-    int iters_before = 0;
-    read_scalars(c);
-    iters_before = c.hflags[F_ITERS];
-    if (c.hflags[F_DONE] == 2) { status = IPMG_E_BREAKDOWN; break; }
-    int done = 0;
+    // pipeline: keep one iteration in flight while waiting for the previous one's flag
+    const int iters_before = restarts ? c.hflags[F_ITERS] : 0;
+    unsigned seq[2] = {0, 0};
+    int enq = 0;
     int slot = 0;
-    enq = 0;
     while (iters_before + enq < maxit) {
-      c.flag_dst = c.hflags + F_COUNT * (1 + slot);   // the last kernel writes the flags there ...
+      seq[slot] = ++c.step_seq;
+      const FlagDst dst{&c.box->slot[slot], seq[slot]};   // the last kernel writes the flag there ...
+      c.flag_dst = dst;
       c.flag_written = false;
       pcg_iteration(c, op, n, gate, enq == 0 ? 1 : 0);
-      if (!c.flag_written)                               // ... or they are copied
-        IPMG_HIP(hipMemcpyAsync(c.hflags + F_COUNT * (1 + slot), c.red.flags, sizeof(int) * F_COUNT,
-                                hipMemcpyDeviceToHost, c.stream));
-      c.flag_dst = nullptr;
-      IPMG_HIP(hipEventRecord(slot ? c.ev1 : c.ev0, c.stream));
+      if (!c.flag_written) vflag_slot(c.stream, c.red, dst);   // ... or a launch of its own
+      c.flag_dst = FlagDst{};
+      IPMG_HIP(hipGetLastError());
       ++enq;
       if (enq >= 2) {
-        IPMG_HIP(hipEventSynchronize(slot ? c.ev0 : c.ev1));
-        if (c.hflags[F_COUNT * (1 + (slot ^ 1)) + F_DONE]) { done = 1; break; }
+        const int s = slot ^ 1;
+        const unsigned long long* p = &c.box->slot[s];
+        wait_for(c, [&] { return (unsigned)(host_load(p) >> 32) == seq[s]; });
+        if ((unsigned)host_load(p)) break;
       }
       slot ^= 1;
     }
@@ -649,33 +676,26 @@ int pcg(Ctx& c, int op, const double* b, double* u, double rtol, int maxit, ipmg
     // kernel, gated or not, applies and clears it), whose p is c.pp.
     if (c.ops->dir_folds_solution(c)) vzflush(c.stream, c.pu, c.pp, n, c.red);
     IPMG_HIP(hipGetLastError());
-    read_scalars(c);
-    (void)done;
+    confirm();
     if (c.hflags[F_DONE] == 2) { status = IPMG_E_BREAKDOWN; break; }
     if (c.hflags[F_DONE] != 1) { status = IPMG_E_NOT_CONVERGED; break; }
-    // confirm with the true residual; restart from it if the recurrence drifted
-    c.ops->fine_apply64(c, op, c.pu, c.pq, nullptr);
-    vsub_norm(c.stream, c.pq, c.pb, c.pr, n, c.red, S_RN2);
-    read_scalars(c);
-    if (c.hscal[S_RN2] <= c.hscal[S_TOL2]) { converged = true; break; }
-    if (c.hflags[F_ITERS] >= maxit) { status = IPMG_E_NOT_CONVERGED; break; }
+    // the true residual; restart from it if the recurrence drifted
+    if (c.hscal[S_TMP2] <= c.hscal[S_TOL2]) { converged = true; break; }
+    if (c.hflags[F_ITERS] >= maxit) {
+      status = IPMG_E_NOT_CONVERGED;
+      c.hscal[S_RN2] = c.hscal[S_TMP2];
+      break;
+    }
     ++restarts;
+    std::swap(c.pr, c.pt);
     vset_tol(c.stream, c.red, rtol);
     pcg_restart_direction(c, op, n);
   }
-  read_scalars(c);
-  const double relres_rec = std::sqrt(c.hscal[S_RN2] / bn2);
-  // true residual and b'u at exit
-  c.ops->fine_apply64(c, op, c.pu, c.pq, nullptr);
-  vsub_norm(c.stream, c.pq, c.pb, c.pt, n, c.red, S_TMP2);
-  vdot(c.stream, c.pb, c.pu, n, c.red, S_TMP3, nullptr);
-  IPMG_HIP(hipMemcpyAsync(u, c.pu, sizeof(double) * n, hipMemcpyDeviceToDevice, c.stream));
-  read_scalars(c);
   auto t1 = std::chrono::steady_clock::now();
   inf.iters = c.hflags[F_ITERS];
   inf.restarts = restarts;
   inf.status = status;
-  inf.relres = relres_rec;
+  inf.relres = std::sqrt((converged ? c.hscal[S_TMP2] : c.hscal[S_RN2]) / bn2);
   inf.true_relres = std::sqrt(c.hscal[S_TMP2] / bn2);
   inf.bu = c.hscal[S_TMP3];
   inf.solve_ms = std::chrono::duration<double, std::milli>(t1 - t0).count();
@@ -989,9 +1009,8 @@ int simp_ip_step(Ctx& c, const double* f, const ipmg_ip_params& p, double rmin, 
   c.ops->filter(c, rmin, c.simp_a, c.simp_t, 1);
   IPMG_HIP(hipMemsetAsync(c.red.flags + F_BAD, 0, sizeof(int), c.stream));
   c.ops->simp_recover(c, c.simp_t, c.ipD, st.x, st.phi, st.psi, st.s, st.r, p.xbar, p.frac, p.step_all_blocks);
-  double dlam = 0.0;
-  IPMG_HIP(hipMemcpyAsync(&dlam, c.ipD + d.nslots, sizeof(double), hipMemcpyDeviceToHost, c.stream));
-  read_scalars(c);
+  read_scalars(c, c.ipD + d.nslots);
+  const double dlam = c.box->extra;
   const double alpha = c.hscal[S_ALPHA];
   inf.alpha = alpha;
   if (!(alpha >= 1e-14) || !std::isfinite(dlam) || c.hflags[F_BAD]) {
@@ -1043,15 +1062,15 @@ int ip_init(Ctx& c, const double* f, const ipmg_ip_params& p, ipmg_ip_state& st,
 
 void ip_prepare(Ctx& c, const double* f, const ipmg_ip_params& p, const ipmg_ip_state& st) {
   ensure_z_buffers(c);
-  set_density(c, st.x);
+  load_density(c, st.x);
   c.ipV = p.V;
-  IPMG_HIP(hipMemsetAsync(c.red.flags + F_BAD, 0, sizeof(int), c.stream));
   if (c.hu) vmask_copy(c.stream, st.u, c.hu, c.fine().nslots, c.fine().nslots, c.dim, c.fine().nx1, c.red, S_QY);
   c.ops->ip_elements(c, st.u, st.x, st.phi, st.psi, st.lam, st.s, st.r, p.xbar);
   c.ops->fine_apply64(c, IPMG_OP_K, st.u, c.ipKu, nullptr);
   c.ops->ip_nodes(c, c.ipKu, f, st.u, c.ipRhs);
   IPMG_HIP(hipGetLastError());
   read_scalars(c);
+  check_density(c);
   IPMG_REQUIRE(!c.hflags[F_BAD], IPMG_E_DOMAIN, "interior-point iterate left the interior or is not finite");
   c.cZ = c.hscal[S_TMP0];
   c.have_z = true;
@@ -1092,9 +1111,8 @@ int ip_step(Ctx& c, const double* f, const ipmg_ip_params& p, ipmg_ip_state& st,
   }
   IPMG_HIP(hipMemsetAsync(c.red.flags + F_BAD, 0, sizeof(int), c.stream));
   c.ops->ip_recover(c, c.ipD, st.x, st.phi, st.psi, st.s, st.r, p.xbar, p.frac, p.step_all_blocks);
-  double dlam = 0.0;
-  IPMG_HIP(hipMemcpyAsync(&dlam, c.ipD + d.nslots, sizeof(double), hipMemcpyDeviceToHost, c.stream));
-  read_scalars(c);
+  read_scalars(c, c.ipD + d.nslots);
+  const double dlam = c.box->extra;
   const double alpha = c.hscal[S_ALPHA];
   inf.alpha = alpha;
   // a non-finite entry of (d_u, d_lambda, d_x, d_phi, d_psi) sets F_BAD: the

@@ -440,7 +440,7 @@ struct TailArgs {
   TailPcg pcg;
   int r64_off;          // LDS place (in doubles) of the FP64 residual
   const double* dot64;  // PCG ratio with the result (finest level only)
-  int* hflags;
+  FlagDst hflags;
 };
 
 // q / d for the node counts of the tail (q < 2^16, rd = 1 / d): the quotient's
@@ -660,12 +660,6 @@ struct TailStep {
   }
 };
 
-// The flags for the host, which reads them behind an event that follows the kernel.
-__device__ inline void tail_flags(const Red& red, int* __restrict__ h) {
-#pragma unroll
-  for (int f = 0; f < F_COUNT; ++f) h[f] = red.flags[f];
-}
-
 template <int DIM, typename T>
 __global__ __launch_bounds__(TailNT<T>::value) void k_tail(TailArgs<T> A, Red red, const int* gate) {
   constexpr int NT = TailNT<T>::value;
@@ -695,7 +689,7 @@ __global__ __launch_bounds__(TailNT<T>::value) void k_tail(TailArgs<T> A, Red re
     }
   }
   if (stop) {
-    if (A.hflags && tid == 0) tail_flags(red, A.hflags);
+    if (A.hflags.p && tid == 0) flags_to_host(red, A.hflags);
     return;
   }
   const int pre_buf = (A.nu_pre - 1) & 1;     // iterate buffer that holds z after the pre-smoothing
@@ -740,7 +734,7 @@ __global__ __launch_bounds__(TailNT<T>::value) void k_tail(TailArgs<T> A, Red re
           if (bad) {
             red.flags[F_DONE] = 2;
             red.flags[F_STATUS] = IPMG_E_BREAKDOWN;
-            if (A.hflags) tail_flags(red, A.hflags);
+            if (A.hflags.p) flags_to_host(red, A.hflags);
           } else {
             red.scal[S_ALPHA] = alpha;
             ratio[0] = rho;
@@ -780,7 +774,7 @@ __global__ __launch_bounds__(TailNT<T>::value) void k_tail(TailArgs<T> A, Red re
         const bool done = !isfinite(s[0]) || s[0] <= tol2;
         if (tid == 0) {
           rn2_finish(s[0], red, false);
-          if (done && A.hflags) tail_flags(red, A.hflags);
+          if (done && A.hflags.p) flags_to_host(red, A.hflags);
         }
         if (done) return;
       } else {
@@ -928,7 +922,7 @@ __global__ __launch_bounds__(TailNT<T>::value) void k_tail(TailArgs<T> A, Red re
       }
     }
   }
-  if (A.hflags && tid == 0) tail_flags(red, A.hflags);
+  if (A.hflags.p && tid == 0) flags_to_host(red, A.hflags);
 }
 
 // Damping estimates of the tail's levels 1..top, one workgroup each, the vectors in LDS.

@@ -37,7 +37,15 @@ void vlincomb(hipStream_t st, double* out, double a, const double* x, double b, 
               int64_t n);   // out = a x + b y (out may alias x or y)
 void vlam_row(hipStream_t st, double* y, const double* v, const Red& red, int sidx, double c,
               int64_t n);   // y[n] = scal[sidx] + c v[n]
-void vcopy_positive(hipStream_t st, const double* src, double* dst, int64_t n, const Red& red);
+// dst = src, dstf = (float) src (unless null); flags[F_BAD] set unless all positive and finite
+void vcopy_positive(hipStream_t st, const double* src, double* dst, float* dstf, int64_t n, const Red& red);
+// Scalars, flags and *extra (may be null) into the host box, then its sequence number.
+void vpublish(hipStream_t st, const Red& red, const double* extra, HostBox* box, unsigned long long seq);
+void vflag_slot(hipStream_t st, const Red& red, FlagDst dst);
+// Start of a PCG solve: pb = b, pu = u (clamped slots 0, flags[F_BAD] set if not
+// finite), scal[S_BN2] = ||b||^2, scal[S_TOL2], scal[S_FLEX].
+void vpcg_load(hipStream_t st, const double* b, const double* u, double* pb, double* pu, int64_t n, int64_t nslots,
+               int dim, int nx1, const Red& red, double rtol, double flex);
 void vset_omega(hipStream_t st, const Red& red, double* w, double* rho, int s_vav, int s_vdv, double omega,
                 double product);
 void vfill_small(hipStream_t st, double* w, int n, double value);   // n <= 64

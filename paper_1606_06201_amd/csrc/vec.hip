@@ -195,16 +195,58 @@ __global__ __launch_bounds__(BS) void k_fill(double* __restrict__ dst, double va
   for (int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x; t < n; t += (int64_t)gridDim.x * BS) dst[t] = value;
 }
 
-// dst = src; flags[F_BAD] = 1 unless every entry is finite and > 0.
+// dst = src, dstf = (float) src (unless null); flags[F_BAD] and [F_XBAD] = 1 unless
+// every entry is finite and > 0.
 __global__ __launch_bounds__(BS) void k_copy_positive(const double* __restrict__ src, double* __restrict__ dst,
-                                                      int64_t n, Red red) {
+                                                      float* __restrict__ dstf, int64_t n, Red red) {
   int bad = 0;
   for (int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x; t < n; t += (int64_t)gridDim.x * BS) {
     const double v = src[t];
     if (!(v > 0.0) || !isfinite(v)) bad = 1;
     dst[t] = v;
+    if (dstf) dstf[t] = (float)v;
+  }
+  if (bad) red.flags[F_BAD] = red.flags[F_XBAD] = 1;
+}
+
+__global__ __launch_bounds__(64) void k_publish(Red red, const double* extra, HostBox* box, unsigned long long seq) {
+  const int t = threadIdx.x;
+  if (t < S_COUNT) box->scal[t] = red.scal[t];
+  else if (t < S_COUNT + F_COUNT) box->flags[t - S_COUNT] = red.flags[t - S_COUNT];
+  else if (t == 63 && extra) box->extra = *extra;
+  __threadfence_system();
+  __syncthreads();
+  if (t == 0) __hip_atomic_store(&box->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__global__ void k_flag_slot(Red red, FlagDst dst) {
+  if (threadIdx.x == 0) flags_to_host(red, dst);
+}
+
+__global__ __launch_bounds__(BS) void k_pcg_load(const double* __restrict__ b, const double* __restrict__ u,
+                                                 double* __restrict__ pb, double* __restrict__ pu, int64_t n,
+                                                 int64_t nslots, int dim, int nx1, Red red) {
+  double s = 0.0;
+  int bad = 0;
+  for (int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x; t < n; t += (int64_t)gridDim.x * BS) {
+    const bool clamped = t < nslots && (t / dim) % nx1 == 0;
+    const double v = clamped ? 0.0 : b[t], w = clamped ? 0.0 : u[t];
+    if (!isfinite(v) || !isfinite(w)) bad = 1;
+    pb[t] = v;
+    pu[t] = w;
+    s += v * v;
   }
   if (bad) red.flags[F_BAD] = 1;
+  const double v[1] = {s};
+  block_partials<1>(v, red);
+}
+__global__ __launch_bounds__(BS) void k_pcg_load_fin(Red red, unsigned nblocks, double rtol2, double flex) {
+  double tot[1];
+  sum_partials<1>(red, nblocks, tot);
+  if (threadIdx.x == 0) {
+    red.scal[S_BN2] = tot[0];
+    red.scal[S_TOL2] = rtol2 * tot[0];
+    red.scal[S_FLEX] = flex;
+  }
 }
 
 template <typename TD, typename TS>
@@ -351,8 +393,17 @@ void vlincomb(hipStream_t st, double* out, double a, const double* x, double b, 
 void vlam_row(hipStream_t st, double* y, const double* v, const Red& red, int sidx, double c, int64_t n) {
   k_lam_row<<<1, 64, 0, st>>>(y, v, red, sidx, c, n);
 }
-void vcopy_positive(hipStream_t st, const double* src, double* dst, int64_t n, const Red& red) {
-  k_copy_positive<<<vgrid(n), BS, 0, st>>>(src, dst, n, red);
+void vcopy_positive(hipStream_t st, const double* src, double* dst, float* dstf, int64_t n, const Red& red) {
+  k_copy_positive<<<vgrid(n), BS, 0, st>>>(src, dst, dstf, n, red);
+}
+void vpublish(hipStream_t st, const Red& red, const double* extra, HostBox* box, unsigned long long seq) {
+  k_publish<<<1, 64, 0, st>>>(red, extra, box, seq);
+}
+void vflag_slot(hipStream_t st, const Red& red, FlagDst dst) { k_flag_slot<<<1, 64, 0, st>>>(red, dst); }
+void vpcg_load(hipStream_t st, const double* b, const double* u, double* pb, double* pu, int64_t n, int64_t nslots,
+               int dim, int nx1, const Red& red, double rtol, double flex) {
+  k_pcg_load<<<vgrid(n), BS, 0, st>>>(b, u, pb, pu, n, nslots, dim, nx1, red);
+  k_pcg_load_fin<<<1, BS, 0, st>>>(red, vgrid(n), rtol * rtol, flex);
 }
 void vset_omega(hipStream_t st, const Red& red, double* w, double* rho, int s_vav, int s_vdv, double omega,
                 double product) {
