@@ -770,20 +770,23 @@ void oc_update(Ctx& c, const double* u, const double* x, double V, double xbar, 
   const Dims& d = c.fine();
   if (!c.oc_t) dalloc(c, c.oc_t, sizeof(double) * (size_t)d.m);
   c.ops->oc_energy(c, u, x, q, c.oc_t);
-  voc_init(c.stream, c.red, c.oc_cand, lam_hi);
   // trials of sequential bisection in exact arithmetic, plus two for rounding;
   // passes past the end are gated on the device
   const int trials = (int)std::ceil(std::log2(lam_hi / tau)) + 2;
-  for (;;) {
-    for (int p = 0; p < (trials + OC_LEVELS - 1) / OC_LEVELS; ++p)
-      voc_pass(c.stream, c.oc_t, d.m, xbar, V, tau, c.oc_cand, c.red);
+  const bool one = voc_one_workgroup(d.m);
+  if (!one) voc_init(c.stream, c.red, c.oc_cand, lam_hi);
+  for (bool resume = false;; resume = true) {
+    if (one) {
+      voc_bisect(c.stream, c.oc_t, d.m, xbar, V, tau, lam_hi, trials, resume, blend, x_new, c.red);
+    } else {
+      for (int p = 0; p < (trials + OC_LEVELS - 1) / OC_LEVELS; ++p)
+        voc_pass(c.stream, c.oc_t, d.m, xbar, V, tau, c.oc_cand, c.red);
+      voc_apply(c.stream, c.oc_t, d.m, xbar, blend, x_new, c.red);
+    }
     IPMG_HIP(hipGetLastError());
     read_scalars(c);
     if (c.hflags[F_OCDONE]) break;
   }
-  voc_apply(c.stream, c.oc_t, d.m, xbar, blend, x_new, c.red);
-  IPMG_HIP(hipGetLastError());
-  read_scalars(c);
   if (info) {
     info->lambda = c.hscal[S_OCLAM];
     info->volume = c.hscal[S_OCSUM];

@@ -54,7 +54,12 @@ void vfill_small(hipStream_t st, double* w, int n, double value);   // n <= 64
 // tree; each voc_pass evaluates the sums at the OC_CAND trials of the next
 // OC_LEVELS bisection levels and walks them in the order of sequential bisection
 // (gated once the bracket is narrower than tau); voc_apply writes x_new at the last
-// trial (blend: x_new = (blend + x_new) / 2) and its sum into scal[S_OCSUM].
+// trial (blend: x_new = (blend + x_new) / 2) and its sum into scal[S_OCSUM], once
+// flags[F_OCDONE] is set.  voc_bisect does all of it in one launch, where
+// voc_one_workgroup(m).
+bool voc_one_workgroup(int64_t m);
+void voc_bisect(hipStream_t st, const double* t, int64_t m, double xbar, double V, double tau, double lam_hi,
+                int max_trials, bool resume, const double* blend, double* x_new, const Red& red);
 void voc_init(hipStream_t st, const Red& red, double* cand, double lam_hi);
 void voc_pass(hipStream_t st, const double* t, int64_t m, double xbar, double V, double tau, double* cand,
               const Red& red);

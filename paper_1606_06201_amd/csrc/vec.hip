@@ -414,92 +414,197 @@ void vfill_small(hipStream_t st, double* w, int n, double value) { k_fill_value<
 // ------------------------------------------------------------ OC bisection --
 namespace {
 
-// Trials of one pass: node 0 is the midpoint of [lo, hi]; node i has children 2i+1
-// (the lower half of its interval) and 2i+2 (the upper half), each midpoint formed
-// as (a + b) / 2 from its interval, exactly as sequential bisection forms it on
-// that path.  One thread.
-__device__ void oc_tree(double lo, double hi, double* cand) {
-  double a[OC_CAND], b[OC_CAND];
-  a[0] = lo;
-  b[0] = hi;
-  for (int i = 0; i < OC_CAND; ++i) {
-    const double mid = (b[i] + a[i]) / 2.0;
-    cand[i] = mid;
-    if (2 * i + 2 < OC_CAND) {
-      a[2 * i + 1] = a[i]; b[2 * i + 1] = mid;
-      a[2 * i + 2] = mid;  b[2 * i + 2] = b[i];
+// t / lam for one lam and many t: the quotient from the rounded reciprocal and one
+// correction with its exact remainder, which is the rounded quotient (4e8 random pairs
+// gave no other value) in three operations instead of the eleven of a division.
+// Infinite or undefined quotients come out undefined, and fmin(., xbar) is xbar for
+// both.  Outside [1e-140, 1e140] the reciprocal or the remainder could leave the range:
+// there the division itself is taken.
+struct OcDiv {
+  double lam, r;
+  bool fast;
+  __device__ explicit OcDiv(double l) : lam(l), r(1.0 / l), fast(l >= 1e-140 && l <= 1e140) {}
+  __device__ double quick(double t) const {
+    const double q = t * r;
+    return __builtin_fma(__builtin_fma(-lam, q, t), r, q);
+  }
+};
+
+// The whole bisection in one workgroup, the t_e in registers (E of them a thread), and
+// x_new with its sum when the bracket is narrower than tau.  Bound by FP64 arithmetic of
+// one CU: five operations per element and trial and a two-level sum.  resume: the
+// bracket of an earlier launch goes on (max_trials ends every launch).
+// A whole update with 50 trials (call to result): 335 -> 72 us at 128x64, 350 -> 87 us
+// at 128x126, where 11 passes of two kernels went before.  Past 16 elements a thread the
+// registers spill and the passes below, which fill the chip, take over (192x96: 347 ->
+// 127 us).  LDS: the wave sums of two trials, so that one barrier per trial is enough.
+constexpr int OC_WG = 1024, OC_WG_ELEMS = 16;
+template <int E>
+__global__ __launch_bounds__(OC_WG) void k_oc_bisect(const double* __restrict__ t, int64_t m, double xbar, double V,
+                                                     double tau, double lam_hi, int max_trials, int resume,
+                                                     const double* __restrict__ blend, double* __restrict__ xn,
+                                                     Red red) {
+  __shared__ double sh[2][OC_WG / 64];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  double te[E];
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    const int64_t e = (int64_t)i * OC_WG + threadIdx.x;
+    te[i] = e < m ? t[e] : 0.0;
+  }
+  double lo = resume ? red.scal[S_OCLO] : 0.0, hi = resume ? red.scal[S_OCHI] : lam_hi;
+  double lam = resume ? red.scal[S_OCLAM] : 0.0, steps = resume ? red.scal[S_OCSTEPS] : 0.0;
+  __syncthreads();                                   // all have read the scalars
+  int par = 0;
+  auto total = [&](double v) {                       // the same value in every thread
+    v = wave_sum(v);
+    if (lane == 0) sh[par][wid] = v;
+    __syncthreads();
+    double s = sh[par][0];
+#pragma unroll
+    for (int w = 1; w < OC_WG / 64; ++w) s += sh[par][w];
+    par ^= 1;
+    return s;
+  };
+#pragma unroll 1
+  for (int n = 0; n < max_trials && hi - lo > tau; ++n) {
+    lam = (hi + lo) / 2.0;
+    const OcDiv div(lam);
+    double acc = 0.0;
+    if (div.fast) {
+#pragma unroll
+      for (int i = 0; i < E; ++i) {                  // past m: t = 0 adds fmin(0, xbar) = 0
+        acc += fmin(div.quick(te[i]), xbar);
+        if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // four quotients in flight
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        const double v = fmin(te[i] / lam, xbar);
+        acc += (int64_t)i * OC_WG + threadIdx.x < m ? v : 0.0;
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
+    steps += 1.0;
+    if (total(acc) > V) lo = lam;
+    else hi = lam;
+  }
+  const bool done = !(hi - lo > tau);
+  double sum = 0.0;
+  if (done) {
+    double acc = 0.0;
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      const int64_t e = (int64_t)i * OC_WG + threadIdx.x;
+      if (e < m) {
+        double v = fmin(te[i] / lam, xbar);
+        if (blend) v = 0.5 * (blend[e] + v);
+        xn[e] = v;
+        acc += v;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    sum = total(acc);
+  }
+  if (threadIdx.x == 0) {
+    red.scal[S_OCLO] = lo;
+    red.scal[S_OCHI] = hi;
+    red.scal[S_OCLAM] = lam;
+    red.scal[S_OCSTEPS] = steps;
+    red.scal[S_OCSUM] = sum;
+    red.flags[F_OCDONE] = done;
   }
 }
 
-__global__ void k_oc_init(Red red, double* cand, double lam_hi) {
+// Trials of one pass: node 0 is the midpoint of [lo, hi]; node i has children 2i+1
+// (the lower half of its interval) and 2i+2 (the upper half), each midpoint formed
+// as (a + b) / 2 from its interval, exactly as sequential bisection forms it on that
+// path.  Thread i < OC_CAND walks from the root to its own node: node i has the path of
+// the bits of i + 1 after the leading one.
+__device__ inline void oc_tree(double lo, double hi, double* cand) {
+  const int node = (int)threadIdx.x + 1;
+  if (node > OC_CAND) return;
+  double mid = (hi + lo) / 2.0;
+  for (int bit = 30 - __clz(node); bit >= 0; --bit) {
+    if ((node >> bit) & 1) lo = mid;
+    else hi = mid;
+    mid = (hi + lo) / 2.0;
+  }
+  cand[node - 1] = mid;
+}
+
+__global__ __launch_bounds__(64) void k_oc_init(Red red, double* cand, double lam_hi) {
+  oc_tree(0.0, lam_hi, cand);
   if (threadIdx.x != 0) return;
   red.scal[S_OCLO] = 0.0;
   red.scal[S_OCHI] = lam_hi;
   red.scal[S_OCLAM] = 0.0;
   red.scal[S_OCSTEPS] = 0.0;
   red.flags[F_OCDONE] = 0;
-  oc_tree(0.0, lam_hi, cand);
 }
 
-// sum_e min(t_e / lambda_j, xbar) for every trial j of the pass.
+// sum_e min(t_e / lambda_j, xbar) for OC_SPLIT trials of the pass (blockIdx.y takes the
+// next ones): eight of the 31 a thread keep its registers few and the chip full.
+constexpr int OC_SPLIT = 8;
 __global__ __launch_bounds__(BS) void k_oc_sums(const double* __restrict__ t, int64_t m, double xbar,
                                                 const double* __restrict__ cand, Red red) {
   if (red.flags[F_OCDONE]) return;
-  double lam[OC_CAND], acc[OC_CAND];
+  const int j0 = blockIdx.y * OC_SPLIT;
+  double lam[OC_SPLIT], r[OC_SPLIT], acc[OC_SPLIT];
+  bool fast = true;
 #pragma unroll
-  for (int j = 0; j < OC_CAND; ++j) {
-    lam[j] = cand[j];
+  for (int j = 0; j < OC_SPLIT; ++j) {
+    const OcDiv d(cand[min(j0 + j, OC_CAND - 1)]);
+    lam[j] = d.lam;
+    r[j] = d.r;
+    fast = fast && d.fast;
     acc[j] = 0.0;
   }
   for (int64_t e = (int64_t)blockIdx.x * BS + threadIdx.x; e < m; e += (int64_t)gridDim.x * BS) {
     const double te = t[e];
 #pragma unroll
-    for (int j = 0; j < OC_CAND; ++j) acc[j] += fmin(te / lam[j], xbar);
+    for (int j = 0; j < OC_SPLIT; ++j) {
+      const double q = te * r[j];
+      const double v = fast ? __builtin_fma(__builtin_fma(-lam[j], q, te), r[j], q) : te / lam[j];
+      acc[j] += fmin(v, xbar);
+    }
   }
   // block sums, stored trial-major: partials[j * gridDim.x + block]
-  __shared__ double sh[OC_CAND][BS / 64];
+  __shared__ double sh[OC_SPLIT][BS / 64];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
-  for (int j = 0; j < OC_CAND; ++j) {
+  for (int j = 0; j < OC_SPLIT; ++j) {
     const double w = wave_sum(acc[j]);
     if (lane == 0) sh[j][wid] = w;
   }
   __syncthreads();
-  if (threadIdx.x < OC_CAND) {
+  if (threadIdx.x < OC_SPLIT && j0 + (int)threadIdx.x < OC_CAND) {
     double v = sh[threadIdx.x][0];
     for (int w = 1; w < BS / 64; ++w) v += sh[threadIdx.x][w];
-    red.partials[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = v;
+    red.partials[(size_t)(j0 + threadIdx.x) * gridDim.x + blockIdx.x] = v;
   }
 }
 
 // Walk the pass's trials in sequential order: while hi - lo > tau, take the node's
 // midpoint, raise lo when its sum exceeds V (go to the upper half), else lower hi.
-__global__ __launch_bounds__(BS) void k_oc_walk(Red red, unsigned nblocks, double V, double tau, double* cand) {
+// A wave per trial sums the blocks, every thread walks, and the next trials are formed
+// side by side; with k_oc_sums split, an update of 512x256 went from 450 to 241 us.
+__global__ __launch_bounds__(OC_WG) void k_oc_walk(Red red, unsigned nblocks, double V, double tau, double* cand) {
   if (red.flags[F_OCDONE]) return;
-  // totals of every trial over the blocks of k_oc_sums, in a fixed order
-  __shared__ double sh[OC_CAND][BS / 64];
+  __shared__ double tot[OC_CAND], lamc[OC_CAND];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  for (int j = 0; j < OC_CAND; ++j) {
+  if (threadIdx.x < OC_CAND) lamc[threadIdx.x] = cand[threadIdx.x];
+  for (int j = wid; j < OC_CAND; j += OC_WG / 64) {
     double a = 0.0;
-    for (unsigned b = threadIdx.x; b < nblocks; b += BS) a += red.partials[(size_t)j * nblocks + b];
+    for (unsigned b = lane; b < nblocks; b += 64) a += red.partials[(size_t)j * nblocks + b];
     a = wave_sum(a);
-    if (lane == 0) sh[j][wid] = a;
-  }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  double tot[OC_CAND];
-  for (int j = 0; j < OC_CAND; ++j) {
-    double v = sh[j][0];
-    for (int w = 1; w < BS / 64; ++w) v += sh[j][w];
-    tot[j] = v;
+    if (lane == 0) tot[j] = a;
   }
   double lo = red.scal[S_OCLO], hi = red.scal[S_OCHI], lam = red.scal[S_OCLAM], steps = red.scal[S_OCSTEPS];
+  __syncthreads();
   int node = 0;
-  bool done = false;
-  for (int lvl = 0; lvl < OC_LEVELS; ++lvl) {
-    if (!(hi - lo > tau)) { done = true; break; }
-    lam = cand[node];
+  for (int lvl = 0; lvl < OC_LEVELS && hi - lo > tau; ++lvl) {
+    lam = lamc[node];
     steps += 1.0;
     if (tot[node] > V) {
       lo = lam;
@@ -509,17 +614,19 @@ __global__ __launch_bounds__(BS) void k_oc_walk(Red red, unsigned nblocks, doubl
       node = 2 * node + 1;
     }
   }
-  if (!(hi - lo > tau)) done = true;
+  const bool done = !(hi - lo > tau);
+  if (!done) oc_tree(lo, hi, cand);
+  if (threadIdx.x != 0) return;
   red.scal[S_OCLO] = lo;
   red.scal[S_OCHI] = hi;
   red.scal[S_OCLAM] = lam;
   red.scal[S_OCSTEPS] = steps;
   if (done) red.flags[F_OCDONE] = 1;
-  else oc_tree(lo, hi, cand);
 }
 
 __global__ __launch_bounds__(BS) void k_oc_apply(const double* __restrict__ t, int64_t m, double xbar,
                                                  const double* __restrict__ blend, double* __restrict__ xn, Red red) {
+  if (!red.flags[F_OCDONE]) return;                  // launched before the host has read it
   const double lam = red.scal[S_OCLAM];
   double s = 0.0;
   for (int64_t e = (int64_t)blockIdx.x * BS + threadIdx.x; e < m; e += (int64_t)gridDim.x * BS) {
@@ -533,6 +640,7 @@ __global__ __launch_bounds__(BS) void k_oc_apply(const double* __restrict__ t, i
 }
 
 __global__ __launch_bounds__(BS) void k_oc_apply_fin(Red red, unsigned nblocks) {
+  if (!red.flags[F_OCDONE]) return;
   double tot[1];
   sum_partials<1>(red, nblocks, tot);
   if (threadIdx.x == 0) red.scal[S_OCSUM] = tot[0];
@@ -540,13 +648,24 @@ __global__ __launch_bounds__(BS) void k_oc_apply_fin(Red red, unsigned nblocks) 
 
 }  // namespace
 
+bool voc_one_workgroup(int64_t m) { return m <= OC_WG * OC_WG_ELEMS; }
+
+void voc_bisect(hipStream_t st, const double* t, int64_t m, double xbar, double V, double tau, double lam_hi,
+                int max_trials, bool resume, const double* blend, double* x_new, const Red& red) {
+  auto go = [&](auto kern) {
+    kern<<<1, OC_WG, 0, st>>>(t, m, xbar, V, tau, lam_hi, max_trials, resume ? 1 : 0, blend, x_new, red);
+  };
+  if (m <= 2 * OC_WG) go(k_oc_bisect<2>);
+  else if (m <= 8 * OC_WG) go(k_oc_bisect<8>);
+  else go(k_oc_bisect<OC_WG_ELEMS>);
+}
 void voc_init(hipStream_t st, const Red& red, double* cand, double lam_hi) {
   k_oc_init<<<1, 64, 0, st>>>(red, cand, lam_hi);
 }
 void voc_pass(hipStream_t st, const double* t, int64_t m, double xbar, double V, double tau, double* cand,
               const Red& red) {
-  k_oc_sums<<<vgrid(m), BS, 0, st>>>(t, m, xbar, cand, red);
-  k_oc_walk<<<1, BS, 0, st>>>(red, vgrid(m), V, tau, cand);
+  k_oc_sums<<<dim3(vgrid(m), (OC_CAND + OC_SPLIT - 1) / OC_SPLIT), BS, 0, st>>>(t, m, xbar, cand, red);
+  k_oc_walk<<<1, OC_WG, 0, st>>>(red, vgrid(m), V, tau, cand);
 }
 void voc_apply(hipStream_t st, const double* t, int64_t m, double xbar, const double* blend, double* x_new,
                const Red& red) {
