@@ -132,7 +132,7 @@ int ipmg_apply_K(ipmg_ctx* ctx, const double* v, double* y) {
   return guard(ctx, [&](Ctx& c) {
     if (!c.have_x) throw Error(IPMG_E_STATE, "set the densities first");
     const ipmg::Dims& d = c.fine();
-    ipmg::vmask_copy(c.stream, v, c.pt, d.nslots, d.nslots, c.dim, d.nx1, c.red, ipmg::S_TMP0);
+    ipmg::vmask_copy(c.stream, v, c.pt, d.nslots, d.nslots, c.dim, d.nx1);
     c.ops->fine_apply64(c, IPMG_OP_K, c.pt, y, nullptr);
     IPMG_HIP(hipGetLastError());
     ipmg::sync(c);
@@ -145,7 +145,7 @@ int ipmg_apply_Z(ipmg_ctx* ctx, const double* v, double* y) {
   return guard(ctx, [&](Ctx& c) {
     if (!c.have_z) throw Error(IPMG_E_STATE, "prepare the Newton system first");
     const ipmg::Dims& d = c.fine();
-    ipmg::vmask_copy(c.stream, v, c.pt, d.nslots + 1, d.nslots, c.dim, d.nx1, c.red, ipmg::S_TMP0);
+    ipmg::vmask_copy(c.stream, v, c.pt, d.nslots + 1, d.nslots, c.dim, d.nx1);
     c.ops->fine_apply64(c, IPMG_OP_Z, c.pt, y, nullptr);
     IPMG_HIP(hipGetLastError());
     ipmg::sync(c);

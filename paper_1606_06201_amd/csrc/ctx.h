@@ -147,8 +147,10 @@ struct Ops {
   // precision), formed once per set-up (no-op elsewhere)
   virtual void fine_diag(Ctx& c, int op) = 0;
   // SIMP model (Sec. 9): the density filter (mode 0: out = W in, 1: W' in, 2: W2 in
-  // with (W2)_ji = W_ji^2), and x~^p / p x~^(p-1) E
-  virtual void filter(Ctx& c, double rmin, const double* in, double* out, int mode) = 0;
+  // with (W2)_ji = W_ji^2; 3, 4: its scaled halves, see FilterMode, with x), and
+  // x~^p / p x~^(p-1) E
+  virtual void filter(Ctx& c, double rmin, const double* in, double* out, int mode, const double* x = nullptr,
+                      const int* gate = nullptr) = 0;
   virtual void simp_pow(Ctx& c, const double* xt, double p, double* xp, double* q) = 0;
   // Interior-point method on the SIMP model (Sec. 9), see the kernels in ops_impl.h:
   //   elem: g_e = K0 u_e, E_e = u_e'g_e;  design: F3 from the filtered energy term t,
@@ -163,7 +165,11 @@ struct Ops {
                          const double* g, double* bcoef, double* rcoef) = 0;
   virtual void simp_nodes(Ctx& c, const double* Ku, const double* f, const double* u, const double* g,
                           const double* bcoef, const double* rcoef, double* rhs) = 0;
-  virtual void simp_gather(Ctx& c, const double* g, const double* coef, const double* v, double* y) = 0;
+  virtual void simp_dots(Ctx& c, const double* v, const double* g, const double* cf, double* a,
+                         const int* gate) = 0;
+  // returns the blocks whose partials of b'v_u and v_u'y_u it leaves
+  virtual unsigned simp_gather(Ctx& c, const double* g, const double* coef, const double* v, double* y,
+                               const int* gate) = 0;
   virtual void simp_recover(Ctx& c, const double* btdu, const double* du, const double* x, const double* phi,
                             const double* psi, double s, double r, double xbar, double frac, int all_blocks) = 0;
   // t_e = x_e (u_e'K0u_e)^q of the OC update (Sec. 4)
@@ -287,11 +293,11 @@ struct Ctx {
   double* simp_xt = nullptr;
   double* simp_xp = nullptr;
   // SIMP interior point (Sec. 9): c = p x~^(p-1), g_e = K0 u_e (ND x m), E, work
-  // vectors on the design variables, border/rhs coefficients, PCG vectors (n_slots+1)
+  // vectors on the design variables, border/rhs coefficients
   double *simp_cf = nullptr, *simp_g = nullptr, *simp_E = nullptr, *simp_a = nullptr, *simp_t = nullptr;
   double *simp_b1 = nullptr, *simp_b2 = nullptr, *simp_b3 = nullptr, *simp_bcoef = nullptr, *simp_rcoef = nullptr;
-  double *simp_r = nullptr, *simp_y = nullptr, *simp_p = nullptr, *simp_q = nullptr;
   double simp_corner = 0.0;    // corner of the exact Newton matrix, sum w
+  double simp_rmin = 0.0;      // > 0 during a solve with that matrix: PCG applies it in place of Z
 
   // OC update: t_e = x_e E_e^q (m) and the trial multipliers of a bisection pass
   double* oc_t = nullptr;

@@ -100,10 +100,27 @@ __global__ __launch_bounds__(BS) void k_elem_hv(Dims d, const T* __restrict__ h,
   s[e] = hv;
 }
 
-// g_e = scale * w_e' K0 u_e  (B(u)' w scaled).
+// The modes of element values (nodal order of gather_elem), 3D.
+__device__ inline void elem_modes(const double (&ve)[24], double (&D)[3][8]) {
+  double lo[4][3], hi[4][3], ml[3][4], mh[3][4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      lo[b][c] = ve[b * 3 + c];
+      hi[b][c] = ve[(b + 4) * 3 + c];
+    }
+  mode_plane(lo, ml);
+  mode_plane(hi, mh);
+  mode_layer(ml, mh, D);
+}
+
+// g_e = scale * w_e' K0 u_e  (B(u)' w scaled).  3D: the dot product of the modes of w_e
+// with M times those of u_e (144 sums and some 60 multiply-adds for 600 multiply-adds
+// with K0 read entry by entry): 96x48x40 19.4 -> 6.8 us.
 template <int DIM>
 __global__ __launch_bounds__(BS) void k_elem_sens(Dims d, const double* __restrict__ w, const double* __restrict__ u,
-                                                  double scale, double* __restrict__ g) {
+                                                  double cl, double cm, double scale, double* __restrict__ g) {
   constexpr int ND = Geo<DIM>::ND;
   const int64_t e = (int64_t)blockIdx.x * BS + threadIdx.x;
   if (e >= d.m) return;
@@ -113,12 +130,23 @@ __global__ __launch_bounds__(BS) void k_elem_sens(Dims d, const double* __restri
   gather_elem<DIM>(w, d, ei, ej, ek, we);
   gather_elem<DIM>(u, d, ei, ej, ek, ue);
   double s = 0.0;
+  if constexpr (DIM == 3) {
+    double Dw[3][8], Du[3][8], P[3][8];
+    elem_modes(we, Dw);
+    elem_modes(ue, Du);
+    mode_stiffness(Du, cl, cm, P);
 #pragma unroll
-  for (int r = 0; r < ND; ++r) {
-    double t = 0.0;
+    for (int c = 0; c < 3; ++c)
 #pragma unroll
-    for (int c = 0; c < ND; ++c) t += cK0d[r * ND + c] * ue[c];
-    s += we[r] * t;
+      for (int k = 1; k < 8; ++k) s += Dw[c][k] * P[c][k];
+  } else {
+#pragma unroll
+    for (int r = 0; r < ND; ++r) {
+      double t = 0.0;
+#pragma unroll
+      for (int c = 0; c < ND; ++c) t += cK0d[r * ND + c] * ue[c];
+      s += we[r] * t;
+    }
   }
   g[e] = scale * s;
 }
@@ -152,45 +180,79 @@ __global__ __launch_bounds__(BS) void k_oc_energy(Dims d, const double* __restri
 // (every column of W sums to one).  transpose = 0: out = W in, i.e.
 // out_j = sum_i W^_ji in_i / s_i; transpose = 1: out = W' in, out_i = sum_j W^_ji in_j / s_i.
 // The column sums are formed on the fly from the grid geometry; neighbours in a
-// fixed order, so the result is deterministic.
+// fixed order, so the result is deterministic.  Weights are positive at distances up to
+// R = ceil(rmin) - 1: the loops run over those inside the grid only.
+template <int DIM, class F>
+__device__ inline void filter_patch(const Dims& d, int ei, int ej, int ek, double rmin, int R, F&& f) {
+  const int rz = DIM == 3 ? R : 0;
+  for (int dz = DIM == 3 ? max(-rz, -ek) : 0; dz <= (DIM == 3 ? min(rz, d.nz - 1 - ek) : 0); ++dz) {
+    const int ry = R - abs(dz);
+    for (int dy = max(-ry, -ej); dy <= min(ry, d.ny - 1 - ej); ++dy) {
+      const int rx = ry - abs(dy);
+      for (int dx = max(-rx, -ei); dx <= min(rx, d.nx - 1 - ei); ++dx)
+        f(rmin - (double)(abs(dx) + abs(dy) + abs(dz)), ei + dx, ej + dy, ek + dz);
+    }
+  }
+}
 template <int DIM>
 __device__ inline double filter_colsum(const Dims& d, int ei, int ej, int ek, double rmin, int R) {
   double s = 0.0;
-  for (int dz = (DIM == 3 ? -R : 0); dz <= (DIM == 3 ? R : 0); ++dz)
-    for (int dy = -R; dy <= R; ++dy)
-      for (int dx = -R; dx <= R; ++dx) {
-        const int i = ei + dx, j = ej + dy, k = ek + dz;
-        if (i < 0 || i >= d.nx || j < 0 || j >= d.ny || (DIM == 3 && (k < 0 || k >= d.nz))) continue;
-        s += fmax(0.0, rmin - (double)(abs(dx) + abs(dy) + abs(dz)));
-      }
+  filter_patch<DIM>(d, ei, ej, ek, rmin, R, [&](double w, int, int, int) { s += w; });
   return s;
 }
 
-// mode 0: out = W in; 1: out = W' in; 2: out = W2 in with (W2)_ji = W_ji^2.
-template <int DIM>
+// The column sum of an element depends on its distance to the grid's edges only, up to R
+// of them: every block forms the sums of all (2R+1)^DIM positions in LDS, one or a few a
+// thread, where each thread formed the sum of each of its neighbours.  Bound by the
+// latency of the few passes over the neighbours: rmin = 2, 64x32 6.7 -> 5.4 us (W), W'
+// of 96x48x40 10.6 -> 7.2 us.
+//   FILT_W: out = W in;  FILT_WT: out = W' in;  FILT_W2: out = W2 in, (W2)_ji = W_ji^2;
+//   FILT_WT_SCALED: out = x o (W' in) / s, ready for
+//   FILT_SUM: out_j = x_j sum_i W^_ji in_i (= x o (W (s o in))).
+enum FilterMode { FILT_W = 0, FILT_WT = 1, FILT_W2 = 2, FILT_WT_SCALED = 3, FILT_SUM = 4 };
+constexpr int FILT_RMAX = 4;   // rmin <= 5
+__device__ inline int filter_class(int i, int n, int R) {
+  return n <= 2 * R + 1 || i < R ? i : (n - 1 - i < R ? 2 * R - (n - 1 - i) : R);
+}
+__device__ inline int filter_place(int cl, int n, int R) { return n <= 2 * R + 1 || cl <= R ? cl : n - 1 - (2 * R - cl); }
+template <int DIM, int MODE>
 __global__ __launch_bounds__(BS) void k_filter(Dims d, double rmin, int R, const double* __restrict__ in,
-                                               double* __restrict__ out, int mode) {
+                                               const double* __restrict__ x, double* __restrict__ out,
+                                               const int* gate) {
+  constexpr int TW = 2 * FILT_RMAX + 1;
+  __shared__ double tab[DIM == 3 ? TW * TW * TW : TW * TW];
+  if (gate && *gate) return;
+  const int cx = min(d.nx, 2 * R + 1), cy = min(d.ny, 2 * R + 1), cz = DIM == 3 ? min(d.nz, 2 * R + 1) : 1;
+  if (MODE != FILT_SUM) {
+    for (int t = threadIdx.x; t < cx * cy * cz; t += BS)
+      tab[t] = filter_colsum<DIM>(d, filter_place(t % cx, d.nx, R), filter_place(t / cx % cy, d.ny, R),
+                                  DIM == 3 ? filter_place(t / (cx * cy), d.nz, R) : 0, rmin, R);
+    __syncthreads();
+  }
+  auto colsum = [&](int i, int j, int k) {
+    return tab[((DIM == 3 ? filter_class(k, d.nz, R) : 0) * cy + filter_class(j, d.ny, R)) * cx +
+               filter_class(i, d.nx, R)];
+  };
   const int64_t e = (int64_t)blockIdx.x * BS + threadIdx.x;
   if (e >= d.m) return;
   int ei, ej, ek;
   elem_coords<DIM>(d, e, ei, ej, ek);
   double acc = 0.0;
-  for (int dz = (DIM == 3 ? -R : 0); dz <= (DIM == 3 ? R : 0); ++dz)
-    for (int dy = -R; dy <= R; ++dy)
-      for (int dx = -R; dx <= R; ++dx) {
-        const int i = ei + dx, j = ej + dy, k = ek + dz;
-        if (i < 0 || i >= d.nx || j < 0 || j >= d.ny || (DIM == 3 && (k < 0 || k >= d.nz))) continue;
-        const double w = rmin - (double)(abs(dx) + abs(dy) + abs(dz));
-        if (!(w > 0.0)) continue;
-        const int64_t o = ((int64_t)(DIM == 3 ? k : 0) * d.ny + j) * d.nx + i;
-        if (mode == 1) {
-          acc += w * in[o];
-        } else {
-          const double wc = w / filter_colsum<DIM>(d, i, j, k, rmin, R);
-          acc += mode == 2 ? wc * wc * in[o] : wc * in[o];
-        }
-      }
-  out[e] = mode == 1 ? acc / filter_colsum<DIM>(d, ei, ej, ek, rmin, R) : acc;
+  filter_patch<DIM>(d, ei, ej, ek, rmin, R, [&](double w, int i, int j, int k) {
+    const int64_t o = ((int64_t)(DIM == 3 ? k : 0) * d.ny + j) * d.nx + i;
+    if (MODE == FILT_W || MODE == FILT_W2) {
+      const double wc = w / colsum(i, j, k);
+      acc += MODE == FILT_W2 ? wc * wc * in[o] : wc * in[o];
+    } else {
+      acc += w * in[o];
+    }
+  });
+  if (MODE == FILT_WT) acc /= colsum(ei, ej, ek);
+  if (MODE == FILT_WT_SCALED) {
+    const double s = colsum(ei, ej, ek);
+    acc = acc / s * x[e] / s;
+  }
+  out[e] = MODE == FILT_SUM ? x[e] * acc : acc;
 }
 
 // Workgroups of a kernel (threads per group, static LDS) resident on one CU, from
@@ -590,38 +652,65 @@ __global__ __launch_bounds__(BS) void k_simp_nodes(Dims d, const double* __restr
   block_partials<3>(acc, red);
 }
 
+// a_e = c_e (g_e . v_e): c o (B(u)'v) from the stored g_e = K0 u_e.
+template <int DIM>
+__global__ __launch_bounds__(BS) void k_simp_dots(Dims d, const double* __restrict__ v, const double* __restrict__ g,
+                                                  const double* __restrict__ cf, double* __restrict__ a,
+                                                  const int* gate) {
+  constexpr int ND = Geo<DIM>::ND;
+  if (gate && *gate) return;
+  const int64_t e = (int64_t)blockIdx.x * BS + threadIdx.x;
+  if (e >= d.m) return;
+  int ei, ej, ek;
+  elem_coords<DIM>(d, e, ei, ej, ek);
+  double ve[ND], s = 0.0;
+  gather_elem<DIM>(v, d, ei, ej, ek, ve);
+#pragma unroll
+  for (int r = 0; r < ND; ++r) s += g[r * d.m + e] * ve[r];
+  a[e] = cf[e] * s;
+}
+
 // y_u += sum_e coef_e g_e + b v_lambda on the free slots: the rank-one and border
-// part of Z^ v (coef = c o W (w o W'(c o s)), s_e = g_e . v_e).
+// part of Z^ v (coef = c o W (w o W'(c o s)), s_e = g_e . v_e), and the partials of
+// b'v_u and v_u'y_u (summed by k_simp_row).
 template <int DIM>
 __global__ __launch_bounds__(BS) void k_simp_gather(Dims d, const double* __restrict__ g,
                                                     const double* __restrict__ coef, const double* __restrict__ bZ,
-                                                    const double* __restrict__ v, double* __restrict__ y) {
+                                                    const double* __restrict__ v, double* __restrict__ y, Red red,
+                                                    const int* gate) {
   constexpr int NN = Geo<DIM>::NN;
+  if (gate && *gate) return;
   const Tile tl = xcd_tile();
   const int i = tl.x * 64 + (threadIdx.x & 63);
   const int j = tl.y * (BS / 64) + (threadIdx.x >> 6);
   const int k = tl.z;
-  if (i < 1 || i >= d.nx1 || j >= d.ny1) return;
-  const int64_t q = ((int64_t)k * d.ny1 + j) * d.nx1 + i;
-  double tt[DIM];
+  double acc[2] = {0.0, 0.0};
+  if (i >= 1 && i < d.nx1 && j < d.ny1) {
+    const int64_t q = ((int64_t)k * d.ny1 + j) * d.nx1 + i;
+    double tt[DIM];
 #pragma unroll
-  for (int c = 0; c < DIM; ++c) tt[c] = 0.0;
+    for (int c = 0; c < DIM; ++c) tt[c] = 0.0;
 #pragma unroll
-  for (int qq = 0; qq < NN; ++qq) {
-    const int ex = qq & 1, ey = (qq >> 1) & 1, ez = (qq >> 2) & 1;
-    const int ei = i - 1 + ex, ej = j - 1 + ey, ek = k - 1 + ez;
-    if (ei < 0 || ei >= d.nx || ej < 0 || ej >= d.ny || (DIM == 3 && (ek < 0 || ek >= d.nz))) continue;
-    const int64_t e = ((int64_t)(DIM == 3 ? ek : 0) * d.ny + ej) * d.nx + ei;
-    const int a = loc_index(1 - ex, 1 - ey, DIM == 3 ? 1 - ez : 0);
+    for (int qq = 0; qq < NN; ++qq) {
+      const int ex = qq & 1, ey = (qq >> 1) & 1, ez = (qq >> 2) & 1;
+      const int ei = i - 1 + ex, ej = j - 1 + ey, ek = k - 1 + ez;
+      if (ei < 0 || ei >= d.nx || ej < 0 || ej >= d.ny || (DIM == 3 && (ek < 0 || ek >= d.nz))) continue;
+      const int64_t e = ((int64_t)(DIM == 3 ? ek : 0) * d.ny + ej) * d.nx + ei;
+      const int a = loc_index(1 - ex, 1 - ey, DIM == 3 ? 1 - ez : 0);
 #pragma unroll
-    for (int c = 0; c < DIM; ++c) tt[c] += coef[e] * g[(a * DIM + c) * d.m + e];
+      for (int c = 0; c < DIM; ++c) tt[c] += coef[e] * g[(a * DIM + c) * d.m + e];
+    }
+    const double vl = v[d.nslots];
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) {
+      const int64_t sl = q * DIM + c;
+      const double yv = y[sl] + (tt[c] + bZ[sl] * vl);
+      y[sl] = yv;
+      acc[0] += bZ[sl] * v[sl];
+      acc[1] += v[sl] * yv;
+    }
   }
-  const double vl = v[d.nslots];
-#pragma unroll
-  for (int c = 0; c < DIM; ++c) {
-    const int64_t sl = q * DIM + c;
-    y[sl] += tt[c] + bZ[sl] * vl;
-  }
+  block_partials<2>(acc, red);
 }
 
 // Recovery of the SIMP direction: d_x = w (B^'d_u + d_lambda - G3) with btdu =
@@ -1799,10 +1888,19 @@ struct OpsImpl : Ops {
     else k_power_start<DIM, double><<<lin_grid(d.nslots + 1), BS, 0, c.stream>>>(d, aug, (double*)v);
   }
 
-  void filter(Ctx& c, double rmin, const double* in, double* out, int mode) override {
+  void filter(Ctx& c, double rmin, const double* in, double* out, int mode, const double* x,
+              const int* gate) override {
     const Dims& d = c.fine();
     const int R = (int)std::ceil(rmin) - 1;
-    k_filter<DIM><<<lin_grid(d.m), BS, 0, c.stream>>>(d, rmin, R, in, out, mode);
+    IPMG_REQUIRE(R >= 0 && R <= FILT_RMAX, IPMG_E_INVALID, "filter radius out of range");
+    auto go = [&](auto kern) { kern<<<lin_grid(d.m), BS, 0, c.stream>>>(d, rmin, R, in, x, out, gate); };
+    switch (mode) {
+      case FILT_W: go(k_filter<DIM, FILT_W>); break;
+      case FILT_WT: go(k_filter<DIM, FILT_WT>); break;
+      case FILT_W2: go(k_filter<DIM, FILT_W2>); break;
+      case FILT_WT_SCALED: go(k_filter<DIM, FILT_WT_SCALED>); break;
+      default: go(k_filter<DIM, FILT_SUM>); break;
+    }
   }
   void simp_pow(Ctx& c, const double* xt, double p, double* xp, double* q) override {
     k_simp_pow<<<lin_grid(c.fine().m), BS, 0, c.stream>>>(c.fine().m, xt, p, xp, q);
@@ -1815,7 +1913,8 @@ struct OpsImpl : Ops {
 
   void element_sens(Ctx& c, const double* w, const double* u, double scale, double* g) override {
     const Dims& d = c.fine();
-    k_elem_sens<DIM><<<lin_grid(d.m), BS, 0, c.stream>>>(d, w, u, scale, g);
+    const Fine3<double> o = fine3_op<double>(c, IPMG_OP_K);
+    k_elem_sens<DIM><<<lin_grid(d.m), BS, 0, c.stream>>>(d, w, u, o.cl, o.cm, scale, g);
   }
 
   void ip_elements(Ctx& c, const double* u, const double* x, const double* phi, const double* psi, double lam,
@@ -1879,9 +1978,16 @@ struct OpsImpl : Ops {
     k_simp_nodes<DIM><<<gr, BS, 0, c.stream>>>(d, Ku, f, u, g, bcoef, rcoef, rhs, c.bZ64, c.red);
     k_ip_nodes_fin<<<1, BS, 0, c.stream>>>(c.red, gr.x * gr.y * gr.z, c.ipV, rhs, d.nslots);
   }
-  void simp_gather(Ctx& c, const double* g, const double* coef, const double* v, double* y) override {
+  void simp_dots(Ctx& c, const double* v, const double* g, const double* cf, double* a, const int* gate) override {
     const Dims& d = c.fine();
-    k_simp_gather<DIM><<<node_grid(d), BS, 0, c.stream>>>(d, g, coef, c.bZ64, v, y);
+    k_simp_dots<DIM><<<lin_grid(d.m), BS, 0, c.stream>>>(d, v, g, cf, a, gate);
+  }
+  unsigned simp_gather(Ctx& c, const double* g, const double* coef, const double* v, double* y,
+                       const int* gate) override {
+    const Dims& d = c.fine();
+    const dim3 gr = node_grid(d);
+    k_simp_gather<DIM><<<gr, BS, 0, c.stream>>>(d, g, coef, c.bZ64, v, y, c.red, gate);
+    return gr.x * gr.y * gr.z;
   }
   void simp_recover(Ctx& c, const double* btdu, const double* du, const double* x, const double* phi,
                     const double* psi, double s, double r, double xbar, double frac, int all_blocks) override {

@@ -538,7 +538,7 @@ void vcycle64(Ctx& c, int op, const double* r, double* z) {
   IPMG_REQUIRE(c.hier_op == op, IPMG_E_STATE, "multigrid hierarchy not set up for this operator");
   const Dims& d = c.fine();
   const int64_t n = d.nslots + (op == IPMG_OP_Z ? 1 : 0);
-  vmask_copy(c.stream, r, c.pt, n, d.nslots, c.dim, d.nx1, c.red, S_TMP0);
+  vmask_copy(c.stream, r, c.pt, n, d.nslots, c.dim, d.nx1);
   if (c.fp32) vconvert<float, double>(c.stream, c.pt, (float*)c.lev[c.L - 1].r, n, nullptr);
   else vconvert<double, double>(c.stream, c.pt, (double*)c.lev[c.L - 1].r, n, nullptr);
   void* y = vcycle(c, op, nullptr);
@@ -548,6 +548,23 @@ void vcycle64(Ctx& c, int op, const double* r, double* z) {
   sync(c);
 }
 
+// y = Z^ v (n_slots + 1) of the SIMP interior point (Sec. 9): K^ v_u + B^ D^-1 B^' v_u +
+// b v_lambda, b' v_u + (sum w) v_lambda, with B^' v_u = W'(c o s), s_e = v_e'K0u_e, and
+// B^ t = sum_e c_e (W t)_e K0 u_e.  alpha: also the step length of PCG from v'y.
+static void simp_apply(Ctx& c, const double* v, double* y, bool alpha, const int* gate) {
+  c.ops->fine_apply64(c, IPMG_OP_K, v, y, gate);
+  c.ops->simp_dots(c, v, c.simp_g, c.simp_cf, c.simp_a, gate);
+  c.ops->filter(c, c.simp_rmin, c.simp_a, c.simp_b1, 3, c.ipW, gate);      // w o W'(c o s), over the column sums
+  c.ops->filter(c, c.simp_rmin, c.simp_b1, c.simp_a, 4, c.simp_cf, gate);
+  const unsigned nb = c.ops->simp_gather(c, c.simp_g, c.simp_a, v, y, gate);
+  vsimp_row(c.stream, y, v, c.fine().nslots, c.simp_corner, c.red, nb, alpha, gate);
+}
+static void op_apply(Ctx& c, int op, const double* v, double* y) {
+  if (c.simp_rmin > 0.0) simp_apply(c, v, y, false, nullptr);
+  else c.ops->fine_apply64(c, op, v, y, nullptr);
+}
+static bool folds_solution(const Ctx& c) { return c.simp_rmin == 0.0 && c.ops->dir_folds_solution(c); }
+
 // Enqueue one PCG iteration (all kernels gated on flags[F_DONE]):
 //   p = -y + beta p, q = A p, alpha      (one fused kernel)
 //   z += alpha p, r += alpha q, ||r||^2  (one fused kernel, sets the done flag)
@@ -556,9 +573,11 @@ void vcycle64(Ctx& c, int op, const double* r, double* z) {
 // With the fold, z += alpha p of a step is done by the next step's direction
 // kernel (which reads that p anyway) and, for the last step, by vzflush.
 // With the finest level in the one-workgroup tail, the tail's launch does all that
-// follows the direction kernel.
+// follows the direction kernel.  With the SIMP Newton matrix the direction and the
+// product are kernels of their own (simp_apply) and the tail runs the V-cycle alone.
 static void pcg_iteration(Ctx& c, int op, int64_t n, const int* gate, int first) {
-  if (c.ops->tail_level(c, op) == c.L - 1 && c.L > 1) {
+  const bool simp = c.simp_rmin > 0.0, all_tail = c.ops->tail_level(c, op) == c.L - 1 && c.L > 1;
+  if (all_tail && !simp) {
     c.step_in_tail = true;
     c.ops->dir_apply(c, op, c.yT, c.pp, c.pp2, c.pq, first, gate, nullptr);
     c.step_in_tail = false;
@@ -566,9 +585,15 @@ static void pcg_iteration(Ctx& c, int op, int64_t n, const int* gate, int first)
     c.yT = vcycle_level(c, op, c.L - 1, gate, c.pr);
     return;
   }
-  const bool fold = c.ops->dir_folds_solution(c);
-  c.ops->dir_apply(c, op, c.yT, c.pp, c.pp2, c.pq, first, gate, fold ? c.pu : nullptr);
-  std::swap(c.pp, c.pp2);                                               // c.pp holds the new p
+  const bool fold = folds_solution(c);
+  if (simp) {
+    if (c.fp32) vpcg_dir<float>(c.stream, c.pp, (const float*)c.yT, n, c.red, first, gate);
+    else vpcg_dir<double>(c.stream, c.pp, (const double*)c.yT, n, c.red, first, gate);
+    simp_apply(c, c.pp, c.pq, true, gate);
+  } else {
+    c.ops->dir_apply(c, op, c.yT, c.pp, c.pp2, c.pq, first, gate, fold ? c.pu : nullptr);
+    std::swap(c.pp, c.pp2);                                             // c.pp holds the new p
+  }
   void* rT = c.lev[c.L - 1].r;
   double* z = fold ? nullptr : c.pu;
   {
@@ -578,7 +603,7 @@ static void pcg_iteration(Ctx& c, int op, int64_t n, const int* gate, int first)
     else
       vpcg_update<double>(c.stream, z, c.pr, c.pp, c.pq, (double*)rT, n, c.red, gate);
   }
-  if (c.fold_rn2_fin) {                   // finalized by the V-cycle's first pass
+  if (c.fold_rn2_fin && !all_tail) {      // finalized by the V-cycle's first pass
     c.rn2_fin_blocks = vpcg_update_blocks(n);
     c.rn2_fin_zpend = fold;
   } else {
@@ -586,7 +611,7 @@ static void pcg_iteration(Ctx& c, int op, int64_t n, const int* gate, int first)
   }
   // the finest level's last post-smoothing sweep forms beta (no sweep on a one-level
   // hierarchy: the coarsest solve is the whole V-cycle)
-  const bool fused_beta = c.desc.nu_post >= 1 && c.L > 1;
+  const bool fused_beta = c.desc.nu_post >= 1 && c.L > 1 && !all_tail;
   void* y = vcycle_level(c, op, c.L - 1, gate, fused_beta ? c.pr : nullptr);
   if (!fused_beta) {
     if (c.fp32) vdot_beta<float>(c.stream, c.pr, (const float*)y, n, c.red, gate);
@@ -619,15 +644,22 @@ int pcg(Ctx& c, int op, const double* b, double* u, double rtol, int maxit, ipmg
   const int64_t n = d.nslots + (op == IPMG_OP_Z ? 1 : 0);
   const int* gate = c.red.flags + F_DONE;
   IPMG_HIP(hipMemsetAsync(c.red.flags, 0, sizeof(int) * F_COUNT, c.stream));
-  vpcg_load(c.stream, b, u, c.pb, c.pu, n, d.nslots, c.dim, d.nx1, c.red, rtol, c.desc.pcg_flexible ? 1.0 : 0.0);
+  vpcg_load(c.stream, b, u, c.pb, c.pu, n, d.nslots, c.dim, d.nx1, c.red, rtol,
+            c.desc.pcg_flexible && c.simp_rmin == 0.0 ? 1.0 : 0.0);
   // r = A u - b
-  c.ops->fine_apply64(c, op, c.pu, c.pq, nullptr);
+  op_apply(c, op, c.pu, c.pq);
   vsub_norm(c.stream, c.pq, c.pb, c.pr, n, c.red, S_RN2);
   read_scalars(c);
-  IPMG_REQUIRE(!c.hflags[F_BAD], IPMG_E_DOMAIN, "right-hand side or initial guess is not finite");
   const double bn2 = c.hscal[S_BN2];
   ipmg_pcg_info inf{};
   inf.setup_ms = setup_ms;
+  if (c.hflags[F_BAD] && c.simp_rmin > 0.0) {       // a Newton system that is not finite: no step
+    inf.status = IPMG_E_BREAKDOWN;
+    inf.relres = std::numeric_limits<double>::quiet_NaN();
+    if (info) *info = inf;
+    return inf.status;
+  }
+  IPMG_REQUIRE(!c.hflags[F_BAD], IPMG_E_DOMAIN, "right-hand side or initial guess is not finite");
   if (bn2 == 0.0) {
     IPMG_HIP(hipMemsetAsync(u, 0, sizeof(double) * n, c.stream));
     sync(c);
@@ -637,7 +669,7 @@ int pcg(Ctx& c, int op, const double* b, double* u, double rtol, int maxit, ipmg
   // The residual of the iterate, b'u and the iterate itself, all of it read back at
   // once: the confirmation of a stop is also what the call returns.
   auto confirm = [&] {
-    c.ops->fine_apply64(c, op, c.pu, c.pq, nullptr);
+    op_apply(c, op, c.pu, c.pq);
     vsub_norm(c.stream, c.pq, c.pb, c.pt, n, c.red, S_TMP2);
     vdot(c.stream, c.pb, c.pu, n, c.red, S_TMP3, nullptr);
     IPMG_HIP(hipMemcpyAsync(u, c.pu, sizeof(double) * n, hipMemcpyDeviceToDevice, c.stream));
@@ -674,7 +706,7 @@ int pcg(Ctx& c, int op, const double* b, double* u, double rtol, int maxit, ipmg
     }
     // A pending update belongs to the last enqueued step (any later direction
     // kernel, gated or not, applies and clears it), whose p is c.pp.
-    if (c.ops->dir_folds_solution(c)) vzflush(c.stream, c.pu, c.pp, n, c.red);
+    if (folds_solution(c)) vzflush(c.stream, c.pu, c.pp, n, c.red);
     IPMG_HIP(hipGetLastError());
     confirm();
     if (c.hflags[F_DONE] == 2) { status = IPMG_E_BREAKDOWN; break; }
@@ -822,14 +854,13 @@ int simp_compliance(Ctx& c, const double* x, const double* f, double rmin, doubl
 static void ensure_simp_buffers(Ctx& c) {
   if (c.simp_cf) return;
   const Dims& d = c.fine();
-  const size_t m = (size_t)d.m, n1 = (size_t)d.nslots + 1;
+  const size_t m = (size_t)d.m;
   if (!c.simp_xt) dalloc(c, c.simp_xt, sizeof(double) * m);
   if (!c.simp_xp) dalloc(c, c.simp_xp, sizeof(double) * m);
   for (double** b : {&c.simp_cf, &c.simp_E, &c.simp_a, &c.simp_t, &c.simp_b1, &c.simp_b2, &c.simp_b3, &c.simp_bcoef,
                      &c.simp_rcoef})
     dalloc(c, *b, sizeof(double) * m);
   dalloc(c, c.simp_g, sizeof(double) * (size_t)c.nd * m);
-  for (double** b : {&c.simp_r, &c.simp_y, &c.simp_p, &c.simp_q}) dalloc(c, *b, sizeof(double) * n1);
 }
 
 // x~ = W x, K^ = sum x~^p K_e (set as the densities), c = p x~^(p-1).
@@ -855,7 +886,7 @@ static void simp_prepare(Ctx& c, const double* f, const ipmg_ip_params& p, doubl
   c.ipV = p.V;
   simp_densities(c, st.x, rmin, pexp);
   IPMG_HIP(hipMemsetAsync(c.red.flags + F_BAD, 0, sizeof(int), c.stream));
-  if (c.hu) vmask_copy(c.stream, st.u, c.hu, d.nslots, d.nslots, c.dim, d.nx1, c.red, S_QY);
+  if (c.hu) vmask_copy(c.stream, st.u, c.hu, d.nslots, d.nslots, c.dim, d.nx1);
   c.ops->simp_elem(c, st.u, c.simp_g, c.simp_E);
   vmul(c.stream, c.simp_cf, c.simp_E, c.simp_a, d.m);
   c.ops->filter(c, rmin, c.simp_a, c.simp_t, 1);                         // W'(c o E)
@@ -876,89 +907,17 @@ static void simp_prepare(Ctx& c, const double* f, const ipmg_ip_params& p, doubl
   c.hier_op = -1;
 }
 
-// y = Z^ v (n_slots + 1): K^ v_u + B^ D^-1 B^' v_u + b v_lambda, b' v_u + (sum w) v_lambda,
-// with B^' v_u = W'(c o s), s_e = v_e'K0u_e, and B^ t = sum_e c_e (W t)_e K0 u_e.
-static void simp_apply(Ctx& c, double rmin, const double* u, const double* v, double* y) {
-  const Dims& d = c.fine();
-  c.ops->fine_apply64(c, IPMG_OP_K, v, y, nullptr);
-  c.ops->element_sens(c, v, u, 1.0, c.simp_a);
-  vmul(c.stream, c.simp_cf, c.simp_a, c.simp_a, d.m);
-  c.ops->filter(c, rmin, c.simp_a, c.simp_b1, 1);
-  vmul(c.stream, c.simp_b1, c.ipW, c.simp_b1, d.m);
-  c.ops->filter(c, rmin, c.simp_b1, c.simp_a, 0);
-  vmul(c.stream, c.simp_cf, c.simp_a, c.simp_a, d.m);
-  c.ops->simp_gather(c, c.simp_g, c.simp_a, v, y);
-  vdot(c.stream, c.bZ64, v, d.nslots, c.red, S_TMP4, nullptr);
-  vlam_row(c.stream, y, v, c.red, S_TMP4, c.simp_corner, d.nslots);
-  IPMG_HIP(hipGetLastError());
-}
-
-// Algorithm PCG (the recurrence, stopping test and true-residual restart of pcg)
-// on Z^ with the V-cycle of the prepared hierarchy, from z (from_z) or from 0.
-static int simp_pcg(Ctx& c, double rmin, const double* u, const double* b, double* z, double rtol, int maxit,
-                    bool from_z, ipmg_pcg_info* info) {
-  const Dims& d = c.fine();
-  const int64_t n1 = d.nslots + 1;
-  auto t0 = std::chrono::steady_clock::now();
-  auto dot = [&](const double* a, const double* bb) {
-    vdot(c.stream, a, bb, n1, c.red, S_TMP5, nullptr);
-    double v = 0.0;
-    IPMG_HIP(hipMemcpyAsync(&v, c.red.scal + S_TMP5, sizeof(double), hipMemcpyDeviceToHost, c.stream));
-    sync(c);
-    return v;
-  };
-  double *r = c.simp_r, *y = c.simp_y, *pp = c.simp_p, *q = c.simp_q;
-  ipmg_pcg_info inf{};
-  const double bnorm = std::sqrt(dot(b, b));
-  auto finish = [&](int status, int iters, double rel) {
-    simp_apply(c, rmin, u, z, q);
-    vlincomb(c.stream, q, 1.0, q, -1.0, b, n1);
-    inf.iters = iters;
-    inf.status = status;
-    inf.relres = rel;
-    inf.true_relres = bnorm > 0.0 ? std::sqrt(dot(q, q)) / bnorm : 0.0;
-    inf.solve_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
-    if (info) *info = inf;
-    return status;
-  };
-  if (!from_z) IPMG_HIP(hipMemsetAsync(z, 0, sizeof(double) * n1, c.stream));
-  if (bnorm == 0.0) return finish(IPMG_OK, 0, 0.0);
-  simp_apply(c, rmin, u, z, r);
-  vlincomb(c.stream, r, 1.0, r, -1.0, b, n1);                 // r = A z - b
-  double rel = std::sqrt(dot(r, r)) / bnorm;
-  if (rel <= rtol) return finish(IPMG_OK, 0, rel);
-  vcycle64(c, IPMG_OP_Z, r, y);
-  vlincomb(c.stream, pp, -1.0, y, 0.0, y, n1);
-  double rho = dot(r, y);
-  if (!(rho > 0.0)) return finish(IPMG_E_BREAKDOWN, 0, rel);
-  int iters = 0;
-  while (iters < maxit) {
-    simp_apply(c, rmin, u, pp, q);
-    const double pq = dot(pp, q);
-    if (!(pq > 0.0)) return finish(IPMG_E_BREAKDOWN, iters, rel);
-    const double alpha = rho / pq;
-    vlincomb(c.stream, z, 1.0, z, alpha, pp, n1);
-    vlincomb(c.stream, r, 1.0, r, alpha, q, n1);
-    ++iters;
-    rel = std::sqrt(dot(r, r)) / bnorm;
-    if (rel <= rtol) {
-      simp_apply(c, rmin, u, z, q);
-      vlincomb(c.stream, q, 1.0, q, -1.0, b, n1);
-      if (std::sqrt(dot(q, q)) / bnorm <= rtol) return finish(IPMG_OK, iters, rel);
-      ++inf.restarts;
-      IPMG_HIP(hipMemcpyAsync(r, q, sizeof(double) * n1, hipMemcpyDeviceToDevice, c.stream));
-      vcycle64(c, IPMG_OP_Z, r, y);
-      vlincomb(c.stream, pp, -1.0, y, 0.0, y, n1);
-      rho = dot(r, y);
-      continue;
-    }
-    vcycle64(c, IPMG_OP_Z, r, y);
-    const double rho_new = dot(r, y);
-    if (!(rho_new > 0.0)) return finish(IPMG_E_BREAKDOWN, iters, rel);
-    vlincomb(c.stream, pp, -1.0, y, rho_new / rho, pp, n1);
-    rho = rho_new;
-  }
-  return finish(IPMG_E_NOT_CONVERGED, iters, rel);
+// PCG on the SIMP Newton matrix with the V-cycle of the prepared hierarchy, from z
+// (from_z) or from 0.
+static int simp_pcg(Ctx& c, double rmin, const double* b, double* z, double rtol, int maxit, bool from_z,
+                    ipmg_pcg_info* info) {
+  struct Scope {
+    Ctx& c;
+    Scope(Ctx& cc, double r) : c(cc) { c.simp_rmin = r; }
+    ~Scope() { c.simp_rmin = 0.0; }
+  } scope(c, rmin);
+  if (!from_z) vfill(c.stream, z, 0.0, c.fine().nslots + 1);
+  return pcg(c, IPMG_OP_Z, b, z, rtol, maxit, info);
 }
 
 int simp_ip_init(Ctx& c, const double* f, const ipmg_ip_params& p, double rmin, double pexp, ipmg_ip_state& st,
@@ -986,13 +945,13 @@ int simp_ip_step(Ctx& c, const double* f, const ipmg_ip_params& p, double rmin, 
   double setup_ms = 0.0;
   mg_setup(c, IPMG_OP_Z, &setup_ms);
   ipmg_pcg_info pin{};
-  int ps = simp_pcg(c, rmin, st.u, c.ipRhs, c.ipD, p.pcg_rtol, p.pcg_maxit, false, &pin);
+  int ps = simp_pcg(c, rmin, c.ipRhs, c.ipD, p.pcg_rtol, p.pcg_maxit, false, &pin);
   if (ps == IPMG_E_BREAKDOWN) {   // as ip_step: damping estimated again, continued from the last iterate
     const int first = pin.iters;
     const double first_ms = pin.solve_ms;
     damping_all(c, IPMG_OP_Z, RETRY_POWER_FACTOR * c.power_steps_z, SAFE_PRODUCT_RETRY);
     IPMG_HIP(hipGetLastError());
-    ps = simp_pcg(c, rmin, st.u, c.ipRhs, c.ipD, p.pcg_rtol, p.pcg_maxit, true, &pin);
+    ps = simp_pcg(c, rmin, c.ipRhs, c.ipD, p.pcg_rtol, p.pcg_maxit, true, &pin);
     pin.iters += first;
     pin.solve_ms += first_ms;
     inf.pcg_retries = 1;
@@ -1007,8 +966,7 @@ int simp_ip_step(Ctx& c, const double* f, const ipmg_ip_params& p, double rmin, 
     return ps;
   }
   // d_x = w (B^'d_u + d_lambda - G3), B^'d_u = W'(c o s), s_e = d_u,e'K0u_e
-  c.ops->element_sens(c, c.ipD, st.u, 1.0, c.simp_a);
-  vmul(c.stream, c.simp_cf, c.simp_a, c.simp_a, d.m);
+  c.ops->simp_dots(c, c.ipD, c.simp_g, c.simp_cf, c.simp_a, nullptr);
   c.ops->filter(c, rmin, c.simp_a, c.simp_t, 1);
   IPMG_HIP(hipMemsetAsync(c.red.flags + F_BAD, 0, sizeof(int), c.stream));
   c.ops->simp_recover(c, c.simp_t, c.ipD, st.x, st.phi, st.psi, st.s, st.r, p.xbar, p.frac, p.step_all_blocks);
@@ -1067,7 +1025,7 @@ void ip_prepare(Ctx& c, const double* f, const ipmg_ip_params& p, const ipmg_ip_
   ensure_z_buffers(c);
   load_density(c, st.x);
   c.ipV = p.V;
-  if (c.hu) vmask_copy(c.stream, st.u, c.hu, c.fine().nslots, c.fine().nslots, c.dim, c.fine().nx1, c.red, S_QY);
+  if (c.hu) vmask_copy(c.stream, st.u, c.hu, c.fine().nslots, c.fine().nslots, c.dim, c.fine().nx1);
   c.ops->ip_elements(c, st.u, st.x, st.phi, st.psi, st.lam, st.s, st.r, p.xbar);
   c.ops->fine_apply64(c, IPMG_OP_K, st.u, c.ipKu, nullptr);
   c.ops->ip_nodes(c, c.ipKu, f, st.u, c.ipRhs);

@@ -5,7 +5,6 @@
 namespace ipmg {
 
 void vdot(hipStream_t st, const double* a, const double* b, int64_t n, const Red& red, int sidx, const int* gate);
-void vdot_alpha(hipStream_t st, const double* p, const double* q, int64_t n, const Red& red, const int* gate);
 template <typename T>
 void vdot_beta(hipStream_t st, const double* r, const T* y, int64_t n, const Red& red, const int* gate);
 template <typename T>
@@ -22,8 +21,7 @@ void vzflush(hipStream_t st, double* z, const double* p, int64_t n, const Red& r
 template <typename T>
 void vpcg_dir(hipStream_t st, double* p, const T* y, int64_t n, const Red& red, int first, const int* gate);
 void vsub_norm(hipStream_t st, const double* a, const double* b, double* out, int64_t n, const Red& red, int sidx);
-void vmask_copy(hipStream_t st, const double* src, double* dst, int64_t n, int64_t nslots, int dim, int nx1,
-                const Red& red, int sidx);
+void vmask_copy(hipStream_t st, const double* src, double* dst, int64_t n, int64_t nslots, int dim, int nx1);
 template <typename TD, typename TS>
 void vconvert(hipStream_t st, const TS* src, TD* dst, int64_t n, const int* gate);
 void vset_tol(hipStream_t st, const Red& red, double rtol);
@@ -33,10 +31,10 @@ void vnormalize(hipStream_t st, T* x, int64_t n, const Red& red, int sidx);
 void vfill(hipStream_t st, double* dst, double value, int64_t n);
 void vscale(hipStream_t st, double* v, double a, int64_t n);   // v *= a
 void vmul(hipStream_t st, const double* a, const double* b, double* out, int64_t n);   // out = a o b
-void vlincomb(hipStream_t st, double* out, double a, const double* x, double b, const double* y,
-              int64_t n);   // out = a x + b y (out may alias x or y)
-void vlam_row(hipStream_t st, double* y, const double* v, const Red& red, int sidx, double c,
-              int64_t n);   // y[n] = scal[sidx] + c v[n]
+// y[n] = b'v_u + c v[n], the lambda row of an augmented operator, from the partials of
+// b'v_u and v_u'y_u; alpha: the step length of PCG from v'y.
+void vsimp_row(hipStream_t st, double* y, const double* v, int64_t n, double c, const Red& red, unsigned nblocks,
+               bool alpha, const int* gate);
 // dst = src, dstf = (float) src (unless null); flags[F_BAD] set unless all positive and finite
 void vcopy_positive(hipStream_t st, const double* src, double* dst, float* dstf, int64_t n, const Red& red);
 // Scalars, flags and *extra (may be null) into the host box, then its sequence number.

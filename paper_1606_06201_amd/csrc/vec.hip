@@ -174,21 +174,11 @@ __global__ __launch_bounds__(BS) void k_sub_norm(const double* __restrict__ a, c
 }
 
 // dst = src with clamped slots (nodes with i == 0) zeroed; entries beyond the
-// slots (lambda) copied.  scal[sidx] = ||dst||^2, flags[F_BAD] set if non-finite.
+// slots (lambda) copied.
 __global__ __launch_bounds__(BS) void k_mask_copy(const double* __restrict__ src, double* __restrict__ dst,
-                                                  int64_t n, int64_t nslots, int dim, int nx1, Red red, int sidx) {
-  double s = 0.0;
-  int bad = 0;
-  for (int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x; t < n; t += (int64_t)gridDim.x * BS) {
-    double v = src[t];
-    if (t < nslots && ((t / dim) % nx1) == 0) v = 0.0;
-    if (!isfinite(v)) bad = 1;
-    dst[t] = v;
-    s += v * v;
-  }
-  if (bad) red.flags[F_BAD] = 1;
-  const double v[1] = {s};
-  block_partials<1>(v, red);
+                                                  int64_t n, int64_t nslots, int dim, int nx1) {
+  for (int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x; t < n; t += (int64_t)gridDim.x * BS)
+    dst[t] = t < nslots && ((unsigned)t / (unsigned)dim) % (unsigned)nx1 == 0 ? 0.0 : src[t];
 }
 
 __global__ __launch_bounds__(BS) void k_fill(double* __restrict__ dst, double value, int64_t n) {
@@ -308,10 +298,6 @@ void vdot(hipStream_t st, const double* a, const double* b, int64_t n, const Red
   k_dot<double, double><<<vgrid(n), BS, 0, st>>>(a, b, n, red, gate);
   k_fin1<<<1, BS, 0, st>>>(red, vgrid(n), FIN_STORE, sidx, gate);
 }
-void vdot_alpha(hipStream_t st, const double* p, const double* q, int64_t n, const Red& red, const int* gate) {
-  k_dot<double, double><<<vgrid(n), BS, 0, st>>>(p, q, n, red, gate);
-  k_fin1<<<1, BS, 0, st>>>(red, vgrid(n), FIN_ALPHA, 0, gate);
-}
 template <typename T>
 void vdot_beta(hipStream_t st, const double* r, const T* y, int64_t n, const Red& red, const int* gate) {
   k_dot<double, T><<<vgrid(n), BS, 0, st>>>(r, y, n, red, gate);
@@ -347,10 +333,8 @@ void vsub_norm(hipStream_t st, const double* a, const double* b, double* out, in
   k_sub_norm<<<vgrid(n), BS, 0, st>>>(a, b, out, n, red, sidx);
   k_fin1<<<1, BS, 0, st>>>(red, vgrid(n), FIN_STORE, sidx, nullptr);
 }
-void vmask_copy(hipStream_t st, const double* src, double* dst, int64_t n, int64_t nslots, int dim, int nx1,
-                const Red& red, int sidx) {
-  k_mask_copy<<<vgrid(n), BS, 0, st>>>(src, dst, n, nslots, dim, nx1, red, sidx);
-  k_fin1<<<1, BS, 0, st>>>(red, vgrid(n), FIN_STORE, sidx, nullptr);
+void vmask_copy(hipStream_t st, const double* src, double* dst, int64_t n, int64_t nslots, int dim, int nx1) {
+  k_mask_copy<<<vgrid(n), BS, 0, st>>>(src, dst, n, nslots, dim, nx1);
 }
 template <typename TD, typename TS>
 void vconvert(hipStream_t st, const TS* src, TD* dst, int64_t n, const int* gate) {
@@ -372,26 +356,24 @@ __global__ __launch_bounds__(BS) void k_mul(const double* __restrict__ a, const 
                                             double* __restrict__ out, int64_t n) {
   for (int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x; t < n; t += (int64_t)gridDim.x * BS) out[t] = a[t] * b[t];
 }
-__global__ __launch_bounds__(BS) void k_lincomb(double* __restrict__ out, double a, const double* __restrict__ x,
-                                                double b, const double* __restrict__ y, int64_t n) {
-  for (int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x; t < n; t += (int64_t)gridDim.x * BS)
-    out[t] = a * x[t] + b * y[t];
-}
-// y[n] = scal[sidx] + c v[n]: the lambda row of an augmented operator, b'v_u in scal.
-__global__ void k_lam_row(double* __restrict__ y, const double* __restrict__ v, Red red, int sidx, double c,
-                          int64_t n) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) y[n] = red.scal[sidx] + c * v[n];
+__global__ __launch_bounds__(BS) void k_simp_row(double* __restrict__ y, const double* __restrict__ v, int64_t n,
+                                                 double c, Red red, unsigned nblocks, int alpha, const int* gate) {
+  if (gate && *gate) return;
+  double tot[2];
+  sum_partials<2>(red, nblocks, tot);
+  if (threadIdx.x != 0) return;
+  const double yl = tot[0] + c * v[n];
+  y[n] = yl;
+  if (alpha) finish(FIN_ALPHA, tot[1] + v[n] * yl, red, 0);
 }
 }  // namespace
 void vscale(hipStream_t st, double* v, double a, int64_t n) { k_scale<<<vgrid(n), BS, 0, st>>>(v, a, n); }
 void vmul(hipStream_t st, const double* a, const double* b, double* out, int64_t n) {
   k_mul<<<vgrid(n), BS, 0, st>>>(a, b, out, n);
 }
-void vlincomb(hipStream_t st, double* out, double a, const double* x, double b, const double* y, int64_t n) {
-  k_lincomb<<<vgrid(n), BS, 0, st>>>(out, a, x, b, y, n);
-}
-void vlam_row(hipStream_t st, double* y, const double* v, const Red& red, int sidx, double c, int64_t n) {
-  k_lam_row<<<1, 64, 0, st>>>(y, v, red, sidx, c, n);
+void vsimp_row(hipStream_t st, double* y, const double* v, int64_t n, double c, const Red& red, unsigned nblocks,
+               bool alpha, const int* gate) {
+  k_simp_row<<<1, BS, 0, st>>>(y, v, n, c, red, nblocks, alpha ? 1 : 0, gate);
 }
 void vcopy_positive(hipStream_t st, const double* src, double* dst, float* dstf, int64_t n, const Red& red) {
   k_copy_positive<<<vgrid(n), BS, 0, st>>>(src, dst, dstf, n, red);
