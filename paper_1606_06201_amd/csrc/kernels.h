@@ -2392,7 +2392,8 @@ __device__ inline void galerkin_scatter_q(int q, const double* t, double* row) {
   }
 }
 
-// First coarse level of the 3D augmented system: A_C = sum_q (x_q G_q + g_q g_q'), with
+// First coarse level in 3D: A_C = sum_q (x_q G_q + g_q g_q') (K: without the rank-one
+// part; 128x64x64: 574 us in the row form, 34 us here), with
 // the constant images G_q = W_q' K0 W_q of the unit element and g_q = W_q' h_q.  A
 // block takes 64 coarse elements: wave q forms g_q of all of them into LDS (every h_e
 // read once), then wave w sums rows w, 15-w and 16+w (34 to
@@ -2409,10 +2410,11 @@ __device__ inline void galerkin_gq3(const double* h, double* g) {
   for (int t = 0; t < 24; ++t) g[t] = 0.0;
   galerkin_scatter<3, Q>(h, g);
 }
-static __global__ __launch_bounds__(GZ3_THREADS) void k_galerkin_z3(const double* __restrict__ x,
-                                                                     const double* __restrict__ h, Dims f, Dims c,
-                                                                     double* __restrict__ Ec) {
-  __shared__ double G[8][24][64];
+template <bool Z>
+__global__ __launch_bounds__(GZ3_THREADS) void k_galerkin_z3(const double* __restrict__ x,
+                                                             const double* __restrict__ h, Dims f, Dims c,
+                                                             double* __restrict__ Ec) {
+  __shared__ double G[8][Z ? 24 : 1][64];
   __shared__ double X[8][64];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t C0 = (int64_t)xcd_tile().x * 64 + lane, C = C0 < c.m ? C0 : c.m - 1;
@@ -2420,22 +2422,24 @@ static __global__ __launch_bounds__(GZ3_THREADS) void k_galerkin_z3(const double
   {
     const int qx = w & 1, qy = (w >> 1) & 1, qz = w >> 2;
     const int64_t e = ((int64_t)(2 * CK + qz) * f.ny + (2 * CJ + qy)) * f.nx + (2 * CI + qx);
-    double hv[24], g[24];
-#pragma unroll
-    for (int t = 0; t < 24; ++t) hv[t] = h[(int64_t)t * f.m + e];
     X[w][lane] = x[e];
-    switch (w) {
-      case 0: galerkin_gq3<0>(hv, g); break;
-      case 1: galerkin_gq3<1>(hv, g); break;
-      case 2: galerkin_gq3<2>(hv, g); break;
-      case 3: galerkin_gq3<3>(hv, g); break;
-      case 4: galerkin_gq3<4>(hv, g); break;
-      case 5: galerkin_gq3<5>(hv, g); break;
-      case 6: galerkin_gq3<6>(hv, g); break;
-      default: galerkin_gq3<7>(hv, g); break;
-    }
+    if constexpr (Z) {
+      double hv[24], g[24];
 #pragma unroll
-    for (int t = 0; t < 24; ++t) G[w][t][lane] = g[t];
+      for (int t = 0; t < 24; ++t) hv[t] = h[(int64_t)t * f.m + e];
+      switch (w) {
+        case 0: galerkin_gq3<0>(hv, g); break;
+        case 1: galerkin_gq3<1>(hv, g); break;
+        case 2: galerkin_gq3<2>(hv, g); break;
+        case 3: galerkin_gq3<3>(hv, g); break;
+        case 4: galerkin_gq3<4>(hv, g); break;
+        case 5: galerkin_gq3<5>(hv, g); break;
+        case 6: galerkin_gq3<6>(hv, g); break;
+        default: galerkin_gq3<7>(hv, g); break;
+      }
+#pragma unroll
+      for (int t = 0; t < 24; ++t) G[w][t][lane] = g[t];
+    }
   }
   __syncthreads();
   double xq[8], gr[3][8];
@@ -2443,12 +2447,14 @@ static __global__ __launch_bounds__(GZ3_THREADS) void k_galerkin_z3(const double
   for (int q = 0; q < 8; ++q) {
     xq[q] = X[q][lane];
 #pragma unroll
-    for (int u = 0; u < 3; ++u) gr[u][q] = G[q][u == 0 ? w : (u == 1 ? 15 - w : 16 + w)][lane];
+    for (int u = 0; u < 3; ++u)
+      if constexpr (Z) gr[u][q] = G[q][u == 0 ? w : (u == 1 ? 15 - w : 16 + w)][lane];
   }
   for (int col = w; col < 24; ++col) {
     double gc[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) gc[q] = G[q][col][lane];
+    for (int q = 0; q < 8; ++q)
+      if constexpr (Z) gc[q] = G[q][col][lane];
 #pragma unroll
     for (int u = 0; u < 3; ++u) {
       const int R = u == 0 ? w : (u == 1 ? 15 - w : 16 + w);
@@ -2457,7 +2463,7 @@ static __global__ __launch_bounds__(GZ3_THREADS) void k_galerkin_z3(const double
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         sk = fma(xq[q], cG3d[(q * 24 + R) * 24 + col], sk);
-        sh = fma(gr[u][q], gc[q], sh);
+        if constexpr (Z) sh = fma(gr[u][q], gc[q], sh);
       }
       if (C0 < c.m) Ec[(int64_t)sym_index(R, col, 24) * c.m + C] = sk + sh;
     }
@@ -2504,6 +2510,41 @@ __global__ __launch_bounds__(64 * GAL_WAVES) void k_galerkin(Op op, Dims f, Dims
     if (col >= R) Ec[(int64_t)sym_index(R, col, ND) * c.m + C] = T(row[col]);
 }
 
+// The same for few coarse elements: a block takes one coarse row of 64 elements and a
+// wave one of the sub-elements; the sums over the sub-elements go through LDS (16 KB in
+// 2D, 98 KB in 3D).  The form above takes its sub-elements one after another, a chain of
+// eight waits on memory in 3D.  3D, 128 coarse elements 35 -> 12 us, 1024 34 -> 22 us; 2D,
+// 8 to 512 elements 7.3 -> 4.5 us.  The line at 1024: LDS leaves a CU one 3D block, and
+// the 3072 blocks of 8192 elements would run in twelve rounds of those 12 us, where the
+// form above takes 130 us.
+constexpr int64_t GAL_SPLIT_MAX = 1024;
+template <int DIM, typename T, class Op>
+__global__ __launch_bounds__(64 << DIM) void k_galerkin_split(Op op, Dims f, Dims c, T* __restrict__ Ec) {
+  constexpr int NN = Geo<DIM>::NN, ND = Geo<DIM>::ND;
+  __shared__ double part[NN][ND][64];
+  const unsigned b = xcd_tile().x;
+  const int R = (int)(b % ND), lane = threadIdx.x & 63;
+  const int q = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t C0 = (int64_t)(b / ND) * 64 + lane, C = C0 < c.m ? C0 : c.m - 1;
+  const int CI = (int)(C % c.nx), CJ = (int)((C / c.nx) % c.ny), CK = DIM == 3 ? (int)(C / ((int64_t)c.nx * c.ny)) : 0;
+  const int qx = q & 1, qy = (q >> 1) & 1, qz = (q >> 2) & 1;
+  const int64_t e = ((int64_t)(2 * CK + qz) * f.ny + (2 * CJ + qy)) * f.nx + (2 * CI + qx);
+  double t[ND], row[ND];
+#pragma unroll
+  for (int col = 0; col < ND; ++col) row[col] = 0.0;
+  galerkin_rows<DIM>(op, e, q, R / DIM, R % DIM, t);
+  galerkin_scatter_q<DIM>(q, t, row);
+#pragma unroll
+  for (int col = 0; col < ND; ++col) part[q][col][lane] = row[col];
+  __syncthreads();
+  for (int col = R + q; col < ND; col += NN) {
+    double s = part[0][col][lane];
+#pragma unroll
+    for (int p = 1; p < NN; ++p) s += part[p][col][lane];
+    if (C0 < c.m) Ec[(int64_t)sym_index(R, col, ND) * c.m + C] = T(s);
+  }
+}
+
 // G_q = W_q' K0 W_q for the four sub-elements q of a coarse 2D element (one
 // thread per entry), W_q the bilinear interpolation from the coarse corners to the
 // nodes of sub-element q.
@@ -2529,48 +2570,50 @@ static __global__ void k_galerkin_images2d(const double* __restrict__ K0, double
 // Dense operator of the coarsest level over all slots (+ lambda) into the packed
 // tiles (zeroed, padded), each tile transposed (dense_lowerT_at) and the diagonal
 // tiles in full: rows gathered from the element matrices; clamped rows/columns
-// replaced by identity.  Thread `row` writes the entries (row, col <= row), their
-// mirror images inside a diagonal tile, and for the augmented system entry
-// (n-1, row) of the border row; no two threads write one entry.
+// replaced by identity.  A thread takes a row and one of its 3^DIM neighbour nodes and
+// writes the entries (row, col <= row) of that node, each the sum over the elements the
+// two share, with its mirror image inside a diagonal tile; the node's own thread also
+// writes entry (n-1, row) of the border row of the augmented system.  No two threads
+// write one entry.  Bound by the latency of a few loads: 3D n = 217 52 -> 16 us,
+// n = 676 69 -> 16 us, against one thread a row that added into memory for all of its
+// neighbours one after another.
 template <int DIM, class Op, typename TB>
 __global__ __launch_bounds__(BS) void k_dense_assemble(Op op, Dims d, const TB* border, double corner,
                                                        int aug, double* __restrict__ A, int n) {
-  constexpr int NN = Geo<DIM>::NN;
-  const int row = blockIdx.x * BS + threadIdx.x;
+  constexpr int NB = DIM == 3 ? 27 : 9;
+  const int t = blockIdx.x * BS + threadIdx.x, row = t / NB, nb = t % NB;
   if (row >= n) return;
+  const bool own = nb == NB / 2;
   if (aug && row == n - 1) {
-    A[dense_lowerT_at(row, row)] = corner;
+    if (own) A[dense_lowerT_at(row, row)] = corner;
     return;
   }
   const int q = row / DIM, comp = row % DIM;
   const int i = q % d.nx1, j = (q / d.nx1) % d.ny1, k = DIM == 3 ? q / (d.nx1 * d.ny1) : 0;
-  if (aug) {
+  if (aug && own) {
     const double v = i == 0 ? 0.0 : (double)border[row];
     A[dense_lowerT_at(n - 1, row)] = v;
     if ((n - 1) / DT == row / DT) A[dense_lower_at(n - 1, row)] = v;
   }
   if (i == 0) {
-    A[dense_lowerT_at(row, row)] = 1.0;
+    if (own) A[dense_lowerT_at(row, row)] = 1.0;
     return;
   }
-  for (int qq = 0; qq < NN; ++qq) {
-    const int ex = qq & 1, ey = (qq >> 1) & 1, ez = (qq >> 2) & 1;
-    const int ei = i - 1 + ex, ej = j - 1 + ey, ek = k - 1 + ez;
-    if (ei < 0 || ei >= d.nx || ej < 0 || ej >= d.ny || (DIM == 3 && (ek < 0 || ek >= d.nz))) continue;
-    const int64_t e = ((int64_t)(DIM == 3 ? ek : 0) * d.ny + ej) * d.nx + ei;
-    const int a = loc_index(1 - ex, 1 - ey, DIM == 3 ? 1 - ez : 0);
-    for (int b = 0; b < NN; ++b) {
-      const int bi = ei + loc_x(b), bj = ej + loc_y(b), bk = DIM == 3 ? ek + loc_z(b) : 0;
-      if (bi == 0) continue;
-      const int qb = (bk * d.ny1 + bj) * d.nx1 + bi;
-      for (int cb = 0; cb < DIM; ++cb) {
-        const int col = qb * DIM + cb;
-        if (col > row) continue;
-        const double v = op.entry(e, a * DIM + comp, b * DIM + cb);
-        A[dense_lowerT_at(row, col)] += v;
-        if (col != row && col / DT == row / DT) A[dense_lower_at(row, col)] += v;
-      }
-    }
+  const int bi = i + nb % 3 - 1, bj = j + nb / 3 % 3 - 1, bk = DIM == 3 ? k + nb / 9 - 1 : 0;
+  if (bi < 1 || bi >= d.nx1 || bj < 0 || bj >= d.ny1 || (DIM == 3 && (bk < 0 || bk >= d.nz1))) return;
+  const int qb = (bk * d.ny1 + bj) * d.nx1 + bi;
+#pragma unroll
+  for (int cb = 0; cb < DIM; ++cb) {
+    const int col = qb * DIM + cb;
+    if (col > row) continue;
+    double v = 0.0;
+    for (int ek = DIM == 3 ? max(max(k, bk) - 1, 0) : 0; ek <= (DIM == 3 ? min(min(k, bk), d.nz - 1) : 0); ++ek)
+      for (int ej = max(max(j, bj) - 1, 0); ej <= min(min(j, bj), d.ny - 1); ++ej)
+        for (int ei = max(i, bi) - 1; ei <= min(min(i, bi), d.nx - 1); ++ei)
+          v += op.entry(((int64_t)ek * d.ny + ej) * d.nx + ei, loc_index(i - ei, j - ej, k - ek) * DIM + comp,
+                        loc_index(bi - ei, bj - ej, bk - ek) * DIM + cb);
+    A[dense_lowerT_at(row, col)] = v;
+    if (col != row && col / DT == row / DT) A[dense_lower_at(row, col)] = v;
   }
 }
 

@@ -1856,19 +1856,25 @@ struct OpsImpl : Ops {
     const Dims& cd = c.lev[lev_f - 1].d;
     double* Ec = c.lev[lev_f - 1].E64;
     if (lev_f == c.L - 1) {
-      if (op == IPMG_OP_K) launch_galerkin(c, OpFineK<DIM, double>{c.x64, f.m}, f, cd, Ec);
-      else if (DIM == 3 && cd.m >= 64)   // a full wave of coarse elements
-        k_galerkin_z3<<<(unsigned)((cd.m + 63) / 64), GZ3_THREADS, 0, c.stream>>>(c.x64, c.h64, f, cd, Ec);
+      if (DIM == 3 && cd.m >= 64) {      // a full wave of coarse elements
+        const unsigned g = (unsigned)((cd.m + 63) / 64);
+        if (op == IPMG_OP_K) k_galerkin_z3<false><<<g, GZ3_THREADS, 0, c.stream>>>(c.x64, nullptr, f, cd, Ec);
+        else k_galerkin_z3<true><<<g, GZ3_THREADS, 0, c.stream>>>(c.x64, c.h64, f, cd, Ec);
+      } else if (op == IPMG_OP_K) launch_galerkin(c, OpFineK<DIM, double>{c.x64, f.m}, f, cd, Ec);
       else launch_galerkin(c, OpFineZ<DIM, double>{c.x64, c.h64, f.m}, f, cd, Ec);
     } else {
-      launch_galerkin(c, OpCoarse<DIM, double>{c.lev[lev_f].E64, f.m}, f, cd, Ec);
+      const OpCoarse<DIM, double> o{c.lev[lev_f].E64, f.m};
+      if (cd.m <= GAL_SPLIT_MAX)
+        k_galerkin_split<DIM, double><<<(unsigned)((cd.m + 63) / 64) * Geo<DIM>::ND, 64 << DIM, 0, c.stream>>>(o, f, cd,
+                                                                                                               Ec);
+      else launch_galerkin(c, o, f, cd, Ec);
     }
   }
 
   void dense_assemble(Ctx& c, int op, double* A, int n) override {
     const Dims& d = c.lev[0].d;
     const int aug = op == IPMG_OP_Z;
-    const unsigned g = lin_grid(n);
+    const unsigned g = lin_grid((int64_t)n * (DIM == 3 ? 27 : 9));
     if (c.L == 1) {
       if (op == IPMG_OP_K)
         k_dense_assemble<DIM, OpFineK<DIM, double>, double><<<g, BS, 0, c.stream>>>(
