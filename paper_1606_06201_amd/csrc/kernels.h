@@ -949,8 +949,6 @@ __global__ __launch_bounds__(BS) void k_level(Op op, Dims d, const T* __restrict
   }
 }
 
-// Finalize of a level pass that reduces (augmented border, M_POWER, M_RAYLEIGH,
-// M_JACOBI_BETA): one block of BS threads, launched right after k_level.
 // The stop flag into pinned host memory (one thread): the last kernel of a PCG
 // iteration hands the host its stop test in one store, with the step's number.
 __device__ inline void flags_to_host(const Red& red, const FlagDst& h) {
@@ -958,6 +956,8 @@ __device__ inline void flags_to_host(const Red& red, const FlagDst& h) {
                      __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Finalize of a level pass that reduces (augmented border, M_POWER, M_RAYLEIGH,
+// M_JACOBI_BETA): one block of BS threads, launched right after k_level.
 // hflags (M_JACOBI_BETA, may be empty): host slot that receives the stop flag.
 template <typename T, int MODE>
 __global__ __launch_bounds__(BS) void k_level_fin(const T* __restrict__ v, const T* __restrict__ r,
