@@ -752,6 +752,13 @@ struct OpsImpl : Ops {
   static dim3 node_grid(const Dims& d) {
     return dim3((unsigned)((d.nx1 + 63) / 64), (unsigned)((d.ny1 + BS / 64 - 1) / (BS / 64)), (unsigned)d.nz1);
   }
+  // node_grid for a kernel that leaves a partial per block: refused where a value's
+  // blocks would run over into the next value's slots.
+  static dim3 partial_grid(const Dims& d) {
+    const dim3 g = node_grid(d);
+    IPMG_REQUIRE((int64_t)g.x * g.y * g.z <= MAX_PARTIALS, IPMG_E_INVALID, "grid too large for one reduction");
+    return g;
+  }
   static unsigned lin_grid(int64_t n) { return (unsigned)((n + BS - 1) / BS); }
 
   void element_stiffness(Ctx& c, double* dK0) override {
@@ -1048,9 +1055,8 @@ struct OpsImpl : Ops {
   void launch_level(Ctx& c, const Dims& d, const Op& op, int mode, const T* v, const T* r, T* out,
                     const double* omg, Aug<T> aug, int sidx, int sidx_in, const int* gate,
                     const double* dot64 = nullptr) {
-    const dim3 g = node_grid(d);
+    const dim3 g = partial_grid(d);
     const unsigned nb = g.x * g.y * g.z;
-    IPMG_REQUIRE((int64_t)nb <= MAX_PARTIALS, IPMG_E_INVALID, "grid too large for one reduction");
     const bool fin = (aug.b && mode != M_JACOBI0) || mode == M_POWER || mode == M_RAYLEIGH || mode == M_JACOBI_BETA;
     if constexpr (DIM == 2) {
       // register-blocked tiles pay on large levels; small levels are latency-bound
@@ -1130,6 +1136,7 @@ struct OpsImpl : Ops {
   void launch_fine3(Ctx& c, int op, int mode, const T* v, const T* r, T* out, const double* omg, Aug<T> aug, int sidx,
                     int sidx_in, const int* gate, const double* dot64) {
     const Dims& d = c.fine();
+    partial_grid(d);   // these passes' own blocks are fewer, but the same grids are taken as by the node kernels
     const dim3 g = fine3_grid(c, d).g;
     const unsigned nb = g.x * g.y * g.z;
     IPMG_REQUIRE((int64_t)nb <= MAX_PARTIALS, IPMG_E_INVALID, "grid too large for one reduction");
@@ -1244,7 +1251,7 @@ struct OpsImpl : Ops {
   void launch_dir_apply(Ctx& c, const Op& op, const TY* y, const double* pold, double* p, double* q,
                         Aug<double> aug, int first, const int* gate, double* zs) {
     const Dims& d = c.fine();
-    dim3 g = node_grid(d);
+    dim3 g = partial_grid(d);
     if constexpr (DIM == 2) {
       if (dir_tiled(c)) {
         if (c.nj_dir == 1) return launch_dir2d<TY, Op, 1>(c, op, y, pold, p, q, aug, first, gate, zs);
@@ -1937,7 +1944,7 @@ struct OpsImpl : Ops {
   }
   void ip_nodes(Ctx& c, const double* Ku, const double* f, const double* u, double* rhs) override {
     const Dims& d = c.fine();
-    const dim3 g = node_grid(d);
+    const dim3 g = partial_grid(d);
     k_ip_nodes<DIM><<<g, BS, 0, c.stream>>>(d, Ku, f, u, c.ipG3, c.ipSW, c.h64, c.ipV, rhs, c.bZ64, c.red);
     k_ip_nodes_fin<<<1, BS, 0, c.stream>>>(c.red, g.x * g.y * g.z, c.ipV, rhs, d.nslots);
   }
@@ -1980,7 +1987,7 @@ struct OpsImpl : Ops {
   void simp_nodes(Ctx& c, const double* Ku, const double* f, const double* u, const double* g, const double* bcoef,
                   const double* rcoef, double* rhs) override {
     const Dims& d = c.fine();
-    const dim3 gr = node_grid(d);
+    const dim3 gr = partial_grid(d);
     k_simp_nodes<DIM><<<gr, BS, 0, c.stream>>>(d, Ku, f, u, g, bcoef, rcoef, rhs, c.bZ64, c.red);
     k_ip_nodes_fin<<<1, BS, 0, c.stream>>>(c.red, gr.x * gr.y * gr.z, c.ipV, rhs, d.nslots);
   }
@@ -1991,7 +1998,7 @@ struct OpsImpl : Ops {
   unsigned simp_gather(Ctx& c, const double* g, const double* coef, const double* v, double* y,
                        const int* gate) override {
     const Dims& d = c.fine();
-    const dim3 gr = node_grid(d);
+    const dim3 gr = partial_grid(d);
     k_simp_gather<DIM><<<gr, BS, 0, c.stream>>>(d, g, coef, c.bZ64, v, y, c.red, gate);
     return gr.x * gr.y * gr.z;
   }
