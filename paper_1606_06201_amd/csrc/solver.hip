@@ -129,6 +129,16 @@ static void ensure_z_buffers(Ctx& c) {
   dalloc(c, c.ipKu, sizeof(double) * n1);
 }
 
+// The caller's displacements as the finest-level passes may read them: in 3D these
+// take a clamped node's value as it stands (the 2D ones read it as 0), so the state's
+// copy with zeros there, which also gives the factors h_e.
+static const double* masked_u(Ctx& c, const double* u) {
+  if (!c.hu) return u;
+  const Dims& d = c.fine();
+  vmask_copy(c.stream, u, c.hu, d.nslots, d.nslots, c.dim, d.nx1);
+  return c.hu;
+}
+
 void ctx_init(Ctx& c, const ipmg_desc& d, hipStream_t st) {
   IPMG_REQUIRE(d.dim == 2 || d.dim == 3, IPMG_E_INVALID, "dim must be 2 or 3");
   IPMG_REQUIRE(d.levels >= 1 && d.levels <= 16, IPMG_E_INVALID, "levels must be in [1, 16]");
@@ -888,7 +898,7 @@ static void simp_prepare(Ctx& c, const double* f, const ipmg_ip_params& p, doubl
   c.ipV = p.V;
   simp_densities(c, st.x, rmin, pexp);
   IPMG_HIP(hipMemsetAsync(c.red.flags + F_BAD, 0, sizeof(int), c.stream));
-  if (c.hu) vmask_copy(c.stream, st.u, c.hu, d.nslots, d.nslots, c.dim, d.nx1);
+  const double* um = masked_u(c, st.u);
   c.ops->simp_elem(c, st.u, c.simp_g, c.simp_E);
   vmul(c.stream, c.simp_cf, c.simp_E, c.simp_a, d.m);
   c.ops->filter(c, rmin, c.simp_a, c.simp_t, 1);                         // W'(c o E)
@@ -898,7 +908,7 @@ static void simp_prepare(Ctx& c, const double* f, const ipmg_ip_params& p, doubl
   c.ops->filter(c, rmin, c.simp_a, c.simp_b2, 0);                        // W (G3 o w)
   c.ops->filter(c, rmin, c.ipW, c.simp_b3, 2);                           // W2 w
   c.ops->simp_coef(c, c.simp_cf, c.simp_b1, c.simp_b2, c.simp_b3, c.simp_g, c.simp_bcoef, c.simp_rcoef);
-  c.ops->fine_apply64(c, IPMG_OP_K, st.u, c.ipKu, nullptr);
+  c.ops->fine_apply64(c, IPMG_OP_K, um, c.ipKu, nullptr);
   c.ops->simp_nodes(c, c.ipKu, f, st.u, c.simp_g, c.simp_bcoef, c.simp_rcoef, c.ipRhs);
   IPMG_HIP(hipGetLastError());
   read_scalars(c);
@@ -1027,9 +1037,9 @@ void ip_prepare(Ctx& c, const double* f, const ipmg_ip_params& p, const ipmg_ip_
   ensure_z_buffers(c);
   load_density(c, st.x);
   c.ipV = p.V;
-  if (c.hu) vmask_copy(c.stream, st.u, c.hu, c.fine().nslots, c.fine().nslots, c.dim, c.fine().nx1);
+  const double* um = masked_u(c, st.u);
   c.ops->ip_elements(c, st.u, st.x, st.phi, st.psi, st.lam, st.s, st.r, p.xbar);
-  c.ops->fine_apply64(c, IPMG_OP_K, st.u, c.ipKu, nullptr);
+  c.ops->fine_apply64(c, IPMG_OP_K, um, c.ipKu, nullptr);
   c.ops->ip_nodes(c, c.ipKu, f, st.u, c.ipRhs);
   IPMG_HIP(hipGetLastError());
   read_scalars(c);
