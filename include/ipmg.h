@@ -26,7 +26,10 @@
  *     return host results (status, info structs, host outputs) synchronise it.
  *   - Return value: IPMG_OK (0) or a negative IPMG_E* code.  No C++ exception
  *     crosses this interface.  ipmg_last_error() gives a message.  A context
- *     must not be used from two threads at once.
+ *     must not be used from two threads at once.  Contexts may be of different
+ *     materials (E, nu) and used in any order; calls from several threads run at the
+ *     same time on contexts of one material and dimension, and one after the other
+ *     on contexts of one dimension that differ in it.
  */
 #ifndef IPMG_H
 #define IPMG_H

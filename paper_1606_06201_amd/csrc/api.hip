@@ -20,6 +20,7 @@ template <class F>
 int guard(ipmg_ctx* h, F&& fn) {
   if (!h) return IPMG_E_INVALID;
   try {
+    const ipmg::MaterialUse use(h->c);
     const int rc = fn(h->c);
     if (rc == IPMG_OK) h->c.err.clear();
     return rc;
@@ -48,6 +49,7 @@ int ipmg_create(const ipmg_desc* desc, void* hip_stream, ipmg_ctx** out) {
   try {
     h = new ipmg_ctx();
     ipmg::ctx_init(h->c, *desc, (hipStream_t)hip_stream);
+    const ipmg::MaterialUse use(h->c);   // loaded here, not in the first call
   } catch (const Error& e) {
     if (h) { ipmg::ctx_free(h->c); delete h; }
     return e.code;

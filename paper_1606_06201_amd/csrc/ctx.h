@@ -77,7 +77,10 @@ constexpr int TAIL_MAX_LD = 512;
 struct Ops {
   virtual ~Ops() {}
   virtual void element_stiffness(Ctx& c, double* dK0) = 0;           // into device buffer
-  virtual void upload_k0(const double* K0) = 0;                       // host -> __constant__
+  // Constants of the context's material: formed once from its element matrix, and
+  // copied to the constant memory of the current device.
+  virtual void form_constants(Ctx& c, const double* K0) = 0;
+  virtual void load_constants() = 0;
   // One level pass (see LevelMode) on level lev with operator op.
   // omg: device pointer to the damping weight (Jacobi modes); sidx/sidx_in: scalar
   // slots of the mode's reductions.
@@ -189,6 +192,7 @@ Ops* make_ops3d();
 struct Ctx {
   Arena arena;
   ipmg_desc desc{};
+  int device = 0;
   int dim = 2;
   bool fp32 = true;
   int L = 1;
@@ -391,6 +395,19 @@ int pcg(Ctx& c, int op, const double* b, double* u, double rtol, int maxit, ipmg
 int pcg_noalloc(Ctx& c, int op, const double* b, double* u, double rtol, int maxit, ipmg_pcg_info* info);
 size_t pcg_noalloc_bytes(const Ctx& c);
 void sync(Ctx& c);
+// The context's material in the constant memory that its kernels read, for the life of
+// the object: one array per process and device, shared by all contexts of a dimension.
+// Calls of contexts with the same E and nu run side by side; a call with another
+// material waits, in the order of arrival, until the calls before it have ended, and
+// copies its own constants there.  A call leaves no kernel in flight when it ends.
+struct MaterialUse {
+  Ctx& c;
+  int exceptions;
+  explicit MaterialUse(Ctx& ctx);
+  ~MaterialUse();
+  MaterialUse(const MaterialUse&) = delete;
+  MaterialUse& operator=(const MaterialUse&) = delete;
+};
 // Scalars and flags (and *extra) of the stream's work so far into hscal, hflags and
 // box->extra; waits for them.
 void read_scalars(Ctx& c, const double* extra = nullptr);

@@ -8,8 +8,8 @@
 
 namespace ipmg {
 
-// Element stiffness of the unit element, uploaded once per context
-// (computed by k_element_stiffness below).  Row-major ND x ND.
+// Element stiffness of the unit element (computed by k_element_stiffness below), of
+// the material of the call in progress (MaterialUse).  Row-major ND x ND.
 static __constant__ double cK0d[576];
 static __constant__ float cK0f[576];
 // Galerkin images G_q = W_q' K0 W_q of the unit element on the next coarser grid,

@@ -765,81 +765,82 @@ struct OpsImpl : Ops {
     constexpr int ND = Geo<DIM>::ND;
     k_element_stiffness<DIM><<<(ND * ND + 63) / 64, 64, 0, c.stream>>>(c.desc.E, c.desc.nu, dK0);
   }
-  void upload_k0(const double* K0) override {
-    constexpr int ND = Geo<DIM>::ND;
+  // The element matrix and the Galerkin images of the unit element, in the forms the
+  // kernels read from constant memory: formed and checked once per context
+  // (form_constants), copied to the device by load_constants.
+  double k0d[576] = {0.0}, k14d[14] = {0.0}, g18d[18] = {0.0};
+  float k0f[576] = {0.0f}, k14f[14] = {0.0f}, g18f[18] = {0.0f}, g256f[256] = {0.0f};
+  std::vector<double> g3d;
+
+  void form_constants(Ctx& c, const double* K0) override {
+    constexpr int ND = Geo<DIM>::ND, NQ = Geo<DIM>::NN;
+    for (int t = 0; t < ND * ND; ++t) {
+      k0d[t] = K0[t];
+      k0f[t] = (float)K0[t];
+    }
+    double kmax = 0.0;
+    for (int t = 0; t < ND * ND; ++t) kmax = std::max(kmax, std::fabs(K0[t]));
     if constexpr (DIM == 2) {
-      double kmax = 0.0;
-      for (int t = 0; t < 64; ++t) kmax = std::max(kmax, std::fabs(K0[t]));
       for (int t = 0; t < 64; ++t) {
         const int e = kSq2d[t];
         const double want = e > 0 ? K0[e - 1] : -K0[-e - 1];
         IPMG_REQUIRE(std::fabs(K0[t] - want) <= 1e-12 * kmax, IPMG_E_INVALID,
                      "element matrix lacks the square-element symmetry");
       }
-    }
-    if constexpr (DIM == 3) {
-      double kmax = 0.0, k14[14] = {0.0};
+    } else {
       bool have[14] = {false};
-      for (int t = 0; t < 576; ++t) kmax = std::max(kmax, std::fabs(K0[t]));
       for (int r = 0; r < 24; ++r)
         for (int col = 0; col < 24; ++col) {
           const int e = k0cube_slot(r, col), sl = (e > 0 ? e : -e) - 1;
           const double v = e > 0 ? K0[r * 24 + col] : -K0[r * 24 + col];
-          if (!have[sl]) { k14[sl] = v; have[sl] = true; }
-          IPMG_REQUIRE(std::fabs(v - k14[sl]) <= 1e-12 * kmax, IPMG_E_INVALID,
+          if (!have[sl]) { k14d[sl] = v; have[sl] = true; }
+          IPMG_REQUIRE(std::fabs(v - k14d[sl]) <= 1e-12 * kmax, IPMG_E_INVALID,
                        "element matrix lacks the cube symmetry");
         }
-      float k14f[14];
-      for (int t = 0; t < 14; ++t) k14f[t] = (float)k14[t];
-      IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cK3d), k14, sizeof(double) * 14));
-      IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cK3f), k14f, sizeof(float) * 14));
-      double *dK = nullptr, *dG = nullptr;
-      IPMG_HIP(hipMalloc((void**)&dK, sizeof(double) * 576));
-      IPMG_HIP(hipMalloc((void**)&dG, sizeof(double) * 8 * 576));
-      IPMG_HIP(hipMemcpy(dK, K0, sizeof(double) * 576, hipMemcpyHostToDevice));
-      k_galerkin_images3d<<<8 * 576 / 64, 64>>>(dK, dG);
-      std::vector<double> G(8 * 576);
-      IPMG_HIP(hipMemcpy(G.data(), dG, sizeof(double) * 8 * 576, hipMemcpyDeviceToHost));
-      (void)hipFree(dK);
-      (void)hipFree(dG);
-      IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cG3d), G.data(), sizeof(double) * 8 * 576));
+      for (int t = 0; t < 14; ++t) k14f[t] = (float)k14d[t];
     }
-    float kf[576];
-    for (int t = 0; t < ND * ND; ++t) kf[t] = (float)K0[t];
-    IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cK0d), K0, sizeof(double) * ND * ND));
-    IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cK0f), kf, sizeof(float) * ND * ND));
-    if constexpr (DIM == 2) {
-      double *dK = nullptr, *dG = nullptr;
-      IPMG_HIP(hipMalloc((void**)&dK, sizeof(double) * 64));
-      IPMG_HIP(hipMalloc((void**)&dG, sizeof(double) * 256));
-      IPMG_HIP(hipMemcpy(dK, K0, sizeof(double) * 64, hipMemcpyHostToDevice));
-      k_galerkin_images2d<<<4, 64>>>(dK, dG);
-      double G[256];
-      IPMG_HIP(hipMemcpy(G, dG, sizeof(double) * 256, hipMemcpyDeviceToHost));
-      (void)hipFree(dK);
-      (void)hipFree(dG);
+    // the images, on the GPU
+    double* dK = (double*)c.arena.alloc(sizeof(double) * ND * ND);
+    double* dG = (double*)c.arena.alloc(sizeof(double) * NQ * ND * ND);
+    std::vector<double> G(NQ * ND * ND);
+    IPMG_HIP(hipMemcpyAsync(dK, k0d, sizeof(double) * ND * ND, hipMemcpyHostToDevice, c.stream));
+    if constexpr (DIM == 2) k_galerkin_images2d<<<4, 64, 0, c.stream>>>(dK, dG);
+    else k_galerkin_images3d<<<8 * 576 / 64, 64, 0, c.stream>>>(dK, dG);
+    IPMG_HIP(hipGetLastError());
+    IPMG_HIP(hipMemcpyAsync(G.data(), dG, sizeof(double) * G.size(), hipMemcpyDeviceToHost, c.stream));
+    sync(c);
+    if constexpr (DIM == 3) {
+      g3d = std::move(G);
+    } else {
       // the 18 distinct values, and every entry checked against its signed copy
-      double g18[18] = {0.0};
       bool have[18] = {false};
       double gmax = 0.0;
       for (int t = 0; t < 256; ++t) gmax = std::max(gmax, std::fabs(G[t]));
       for (int t = 0; t < 256; ++t) {
         const int e = kSqG2d[t], k = (e > 0 ? e : -e) - 1;
-        if (!have[k]) { g18[k] = e > 0 ? G[t] : -G[t]; have[k] = true; }
-        const double want = e > 0 ? g18[k] : -g18[k];
+        if (!have[k]) { g18d[k] = e > 0 ? G[t] : -G[t]; have[k] = true; }
+        const double want = e > 0 ? g18d[k] : -g18d[k];
         IPMG_REQUIRE(std::fabs(G[t] - want) <= 1e-12 * gmax, IPMG_E_INVALID,
                      "Galerkin images lack the square-element symmetry");
       }
-      float g18f[18];
-      for (int k = 0; k < 18; ++k) g18f[k] = (float)g18[k];
-      IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cG18d), g18, sizeof(double) * 18));
-      IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cG18f), g18f, sizeof(float) * 18));
-      float g256f[256];
+      for (int k = 0; k < 18; ++k) g18f[k] = (float)g18d[k];
       for (int t = 0; t < 256; ++t) {
         const int e = kSqG2d[t], k = (e > 0 ? e : -e) - 1;
         g256f[t] = e > 0 ? g18f[k] : -g18f[k];
       }
-      IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cG256f), g256f, sizeof(float) * 256));
+    }
+  }
+  void load_constants() override {
+    IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cK0d), k0d, sizeof(k0d)));
+    IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cK0f), k0f, sizeof(k0f)));
+    if constexpr (DIM == 2) {
+      IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cG18d), g18d, sizeof(g18d)));
+      IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cG18f), g18f, sizeof(g18f)));
+      IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cG256f), g256f, sizeof(g256f)));
+    } else {
+      IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cK3d), k14d, sizeof(k14d)));
+      IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cK3f), k14f, sizeof(k14f)));
+      IPMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(cG3d), g3d.data(), sizeof(double) * g3d.size()));
     }
   }
 

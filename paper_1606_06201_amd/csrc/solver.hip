@@ -4,8 +4,10 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <condition_variable>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <mutex>
 
 #include "ctx.h"
@@ -42,6 +44,8 @@ constexpr int POWER_STEPS_Z = 30;
 constexpr int RETRY_POWER_FACTOR = 4;
 constexpr double SAFE_PRODUCT_RETRY = 1.2;
 
+constexpr int MAX_DEVICES = 64;
+
 // Scratch of ipmg_pcg_noalloc: the PCG work vectors and the reduction arrays of a
 // solve, for callers that cannot allocate device memory.  Each GPU the library runs
 // on holds its own copy until the process ends; host code reaches it only through
@@ -52,10 +56,10 @@ static __device__ __align__(256) unsigned char scratch[IPMG_NOALLOC_SCRATCH_BYTE
 // that device current (the array's name is only a host-side stand-in).
 unsigned char* scratch_address() {
   static std::mutex mu;
-  static unsigned char* addr[64] = {nullptr};
+  static unsigned char* addr[MAX_DEVICES] = {nullptr};
   int dev = 0;
   IPMG_HIP(hipGetDevice(&dev));
-  IPMG_REQUIRE(dev >= 0 && dev < 64, IPMG_E_INVALID, "device index out of range");
+  IPMG_REQUIRE(dev >= 0 && dev < MAX_DEVICES, IPMG_E_INVALID, "device index out of range");
   std::lock_guard<std::mutex> lk(mu);
   if (!addr[dev]) {
     void* p = nullptr;
@@ -156,6 +160,8 @@ void ctx_init(Ctx& c, const ipmg_desc& d, hipStream_t st) {
   {
     int dev = 0;
     IPMG_HIP(hipGetDevice(&dev));
+    IPMG_REQUIRE(dev >= 0 && dev < MAX_DEVICES, IPMG_E_INVALID, "device index out of range");
+    c.device = dev;
     IPMG_HIP(hipDeviceGetAttribute(&c.cus, hipDeviceAttributeMultiprocessorCount, dev));
   }
   c.dim = d.dim;
@@ -263,14 +269,77 @@ void ctx_init(Ctx& c, const ipmg_desc& d, hipStream_t st) {
   }
   vfill_small(st, c.omega_dev, c.L, d.omega);
 
-  // element matrix on the GPU, mirrored to the host and to constant memory
+  // element matrix on the GPU, mirrored to the host, and the constants formed from it
   double* dK0 = nullptr;
   dalloc(c, dK0, sizeof(double) * c.nd * c.nd);
   c.ops->element_stiffness(c, dK0);
   IPMG_HIP(hipGetLastError());
   IPMG_HIP(hipMemcpyAsync(c.K0, dK0, sizeof(double) * c.nd * c.nd, hipMemcpyDeviceToHost, st));
   sync(c);
-  c.ops->upload_k0(c.K0);
+  c.ops->form_constants(c, c.K0);
+}
+
+// What the constant memory of a device holds for a dimension, and the calls that use it.
+// Calls enter in the order of arrival (next, serving), so that none waits for ever.
+namespace {
+struct MaterialSlot {
+  std::mutex mu;
+  std::condition_variable cv;
+  bool loaded = false;
+  double E = 0.0, nu = 0.0;
+  int users = 0;
+  unsigned long long next = 0, serving = 0;
+};
+MaterialSlot& material_slot(const Ctx& c) {
+  static MaterialSlot* slots = new MaterialSlot[2 * MAX_DEVICES];   // outlives every thread
+  return slots[2 * c.device + (c.dim == 3 ? 1 : 0)];
+}
+void load_on_device(Ctx& c) {
+  int dev = 0;
+  IPMG_HIP(hipGetDevice(&dev));
+  if (dev != c.device) IPMG_HIP(hipSetDevice(c.device));
+  try {
+    c.ops->load_constants();
+  } catch (...) {
+    if (dev != c.device) (void)hipSetDevice(dev);
+    throw;
+  }
+  if (dev != c.device) IPMG_HIP(hipSetDevice(dev));
+}
+}  // namespace
+
+MaterialUse::MaterialUse(Ctx& ctx) : c(ctx), exceptions(std::uncaught_exceptions()) {
+  MaterialSlot& s = material_slot(c);
+  std::unique_lock<std::mutex> lk(s.mu);
+  auto same = [&] { return s.loaded && s.E == c.desc.E && s.nu == c.desc.nu; };
+  const unsigned long long ticket = s.next++;
+  s.cv.wait(lk, [&] { return s.serving == ticket && (s.users == 0 || same()); });
+  ++s.serving;
+  if (!same()) {
+    s.loaded = false;
+    try {
+      load_on_device(c);
+    } catch (...) {
+      lk.unlock();
+      s.cv.notify_all();
+      throw;
+    }
+    s.loaded = true;
+    s.E = c.desc.E;
+    s.nu = c.desc.nu;
+  }
+  ++s.users;
+  lk.unlock();
+  s.cv.notify_all();
+}
+MaterialUse::~MaterialUse() {
+  if (std::uncaught_exceptions() > exceptions) (void)hipStreamSynchronize(c.stream);   // left by an error
+  MaterialSlot& s = material_slot(c);
+  {
+    std::lock_guard<std::mutex> lk(s.mu);
+    --s.users;
+  }
+  s.cv.notify_all();
 }
 
 void ctx_free(Ctx& c) {
