@@ -314,6 +314,7 @@ __global__ __launch_bounds__(BS) void k_power_start(Dims d, int aug, T* __restri
 // h = sqrt(w) g (rank-one factor of Z), and the sums
 //   scal[S_TMP0..6] = sum w, sum G3 w, sum x, ||G3||^2, ||phi||^2, ||psi||^2,
 //                     phi'x + psi'(xbar - x).
+// Nothing is written where a density is not positive and finite (flags[F_XBAD]).
 template <int DIM, typename T>
 __global__ __launch_bounds__(BS) void k_ip_elements(Dims d, const double* __restrict__ u, const double* __restrict__ x,
                                                     const double* __restrict__ phi, const double* __restrict__ psi,
@@ -321,6 +322,7 @@ __global__ __launch_bounds__(BS) void k_ip_elements(Dims d, const double* __rest
                                                     double* __restrict__ G3o, double* __restrict__ Wo,
                                                     double* __restrict__ SWo, double* __restrict__ h64,
                                                     T* __restrict__ hT, Red red) {
+  if (red.flags[F_XBAD]) return;
   constexpr int ND = Geo<DIM>::ND;
   const int64_t e = (int64_t)blockIdx.x * BS + threadIdx.x;
   double acc[7] = {0, 0, 0, 0, 0, 0, 0};
@@ -380,6 +382,7 @@ __global__ __launch_bounds__(BS) void k_ip_nodes(Dims d, const double* __restric
                                                  const double* __restrict__ SW, const double* __restrict__ h64,
                                                  double V, double* __restrict__ rhs, double* __restrict__ bZ,
                                                  Red red) {
+  if (red.flags[F_XBAD]) return;                 // as k_ip_elements
   constexpr int NN = Geo<DIM>::NN;
   const Tile tl = xcd_tile();
   const int i = tl.x * 64 + (threadIdx.x & 63);

@@ -136,10 +136,10 @@ static void ensure_z_buffers(Ctx& c) {
 // The caller's displacements as the finest-level passes may read them: in 3D these
 // take a clamped node's value as it stands (the 2D ones read it as 0), so the state's
 // copy with zeros there, which also gives the factors h_e.
-static const double* masked_u(Ctx& c, const double* u) {
+static const double* masked_u(Ctx& c, const double* u, const int* gate) {
   if (!c.hu) return u;
   const Dims& d = c.fine();
-  vmask_copy(c.stream, u, c.hu, d.nslots, d.nslots, c.dim, d.nx1);
+  vmask_copy(c.stream, u, c.hu, d.nslots, d.nslots, c.dim, d.nx1, gate);
   return c.hu;
 }
 
@@ -967,7 +967,7 @@ static void simp_prepare(Ctx& c, const double* f, const ipmg_ip_params& p, doubl
   c.ipV = p.V;
   simp_densities(c, st.x, rmin, pexp);
   IPMG_HIP(hipMemsetAsync(c.red.flags + F_BAD, 0, sizeof(int), c.stream));
-  const double* um = masked_u(c, st.u);
+  const double* um = masked_u(c, st.u, nullptr);
   c.ops->simp_elem(c, st.u, c.simp_g, c.simp_E);
   vmul(c.stream, c.simp_cf, c.simp_E, c.simp_a, d.m);
   c.ops->filter(c, rmin, c.simp_a, c.simp_t, 1);                         // W'(c o E)
@@ -1106,7 +1106,9 @@ void ip_prepare(Ctx& c, const double* f, const ipmg_ip_params& p, const ipmg_ip_
   ensure_z_buffers(c);
   load_density(c, st.x);
   c.ipV = p.V;
-  const double* um = masked_u(c, st.u);
+  // densities that turn out bad leave the Newton system of the last call as it was:
+  // what belongs to it is written behind that flag
+  const double* um = masked_u(c, st.u, c.red.flags + F_XBAD);
   c.ops->ip_elements(c, st.u, st.x, st.phi, st.psi, st.lam, st.s, st.r, p.xbar);
   c.ops->fine_apply64(c, IPMG_OP_K, um, c.ipKu, nullptr);
   c.ops->ip_nodes(c, c.ipKu, f, st.u, c.ipRhs);

@@ -21,7 +21,8 @@ void vzflush(hipStream_t st, double* z, const double* p, int64_t n, const Red& r
 template <typename T>
 void vpcg_dir(hipStream_t st, double* p, const T* y, int64_t n, const Red& red, int first, const int* gate);
 void vsub_norm(hipStream_t st, const double* a, const double* b, double* out, int64_t n, const Red& red, int sidx);
-void vmask_copy(hipStream_t st, const double* src, double* dst, int64_t n, int64_t nslots, int dim, int nx1);
+void vmask_copy(hipStream_t st, const double* src, double* dst, int64_t n, int64_t nslots, int dim, int nx1,
+                const int* gate = nullptr);
 template <typename TD, typename TS>
 void vconvert(hipStream_t st, const TS* src, TD* dst, int64_t n, const int* gate);
 void vset_tol(hipStream_t st, const Red& red, double rtol);

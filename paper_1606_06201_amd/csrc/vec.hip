@@ -176,7 +176,8 @@ __global__ __launch_bounds__(BS) void k_sub_norm(const double* __restrict__ a, c
 // dst = src with clamped slots (nodes with i == 0) zeroed; entries beyond the
 // slots (lambda) copied.
 __global__ __launch_bounds__(BS) void k_mask_copy(const double* __restrict__ src, double* __restrict__ dst,
-                                                  int64_t n, int64_t nslots, int dim, int nx1) {
+                                                  int64_t n, int64_t nslots, int dim, int nx1, const int* gate) {
+  if (gate && *gate) return;
   for (int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x; t < n; t += (int64_t)gridDim.x * BS)
     dst[t] = t < nslots && ((unsigned)t / (unsigned)dim) % (unsigned)nx1 == 0 ? 0.0 : src[t];
 }
@@ -333,8 +334,9 @@ void vsub_norm(hipStream_t st, const double* a, const double* b, double* out, in
   k_sub_norm<<<vgrid(n), BS, 0, st>>>(a, b, out, n, red, sidx);
   k_fin1<<<1, BS, 0, st>>>(red, vgrid(n), FIN_STORE, sidx, nullptr);
 }
-void vmask_copy(hipStream_t st, const double* src, double* dst, int64_t n, int64_t nslots, int dim, int nx1) {
-  k_mask_copy<<<vgrid(n), BS, 0, st>>>(src, dst, n, nslots, dim, nx1);
+void vmask_copy(hipStream_t st, const double* src, double* dst, int64_t n, int64_t nslots, int dim, int nx1,
+                const int* gate) {
+  k_mask_copy<<<vgrid(n), BS, 0, st>>>(src, dst, n, nslots, dim, nx1, gate);
 }
 template <typename TD, typename TS>
 void vconvert(hipStream_t st, const TS* src, TD* dst, int64_t n, const int* gate) {
