@@ -800,7 +800,7 @@ int pcg(Ctx& c, int op, const double* b, double* u, double rtol, int maxit, ipmg
       break;
     }
     ++restarts;
-    std::swap(c.pr, c.pt);
+    vsub_norm(c.stream, c.pq, c.pb, c.pr, n, c.red, S_RN2);   // also what a breakdown here reports
     vset_tol(c.stream, c.red, rtol);
     pcg_restart_direction(c, op, n);
   }
