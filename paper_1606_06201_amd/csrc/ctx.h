@@ -18,7 +18,10 @@ struct Arena {
   void* raw(size_t bytes) {
     void* p = nullptr;
     blocks.reserve(blocks.size() + 1);
-    if (hipMalloc(&p, bytes) != hipSuccess) throw Error(IPMG_E_NOMEM, "device allocation failed");
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+      (void)hipGetLastError();                        // reported here, not by the next launch's check
+      throw Error(IPMG_E_NOMEM, "device allocation failed");
+    }
     blocks.push_back(p);
     return p;
   }
@@ -33,6 +36,13 @@ struct Arena {
     void* p = slab + used;
     used += bytes;
     return p;
+  }
+  // Memory for p unless it has some: what a call allocates on first use is asked for one
+  // buffer at a time, so that a call after one that ran out of memory goes on with the
+  // first buffer that is missing.
+  template <typename P>
+  void need(P*& p, size_t bytes) {
+    if (!p) p = (P*)alloc(bytes);
   }
   void release() {
     for (void* p : blocks) (void)hipFree(p);

@@ -1434,10 +1434,8 @@ struct OpsImpl : Ops {
       if (!pow_level(c, k, op)) continue;
       Level& l = c.lev[k];
       const Dims& d = l.d;
-      if (!l.S) {
-        l.S = c.arena.alloc(sizeof(T) * (size_t)sten_size<DIM>(d));
-        l.dinv = c.arena.alloc(sizeof(T) * (size_t)d.nslots);
-      }
+      c.arena.need(l.S, sizeof(T) * (size_t)sten_size<DIM>(d));
+      c.arena.need(l.dinv, sizeof(T) * (size_t)d.nslots);
       const unsigned g = sten_tiles(d);
       T* S = (T*)l.S;
       T* di = (T*)l.dinv;
@@ -1559,11 +1557,9 @@ struct OpsImpl : Ops {
       nblk += p.nblk;
     }
     if (A.nlev == 0) return;
-    if (!c.pow_part) {   // room for every level that can be in the batch
-      size_t tiles = 0;
-      for (int k = 1; k < c.L; ++k) tiles += sten_tiles(c.lev[k].d);
-      c.pow_part = (double*)c.arena.alloc(sizeof(double) * (6 * tiles + 4 * (size_t)c.L));
-    }
+    size_t tiles = 0;    // room for every level that can be in the batch
+    for (int k = 1; k < c.L; ++k) tiles += sten_tiles(c.lev[k].d);
+    c.arena.need(c.pow_part, sizeof(double) * (6 * tiles + 4 * (size_t)c.L));
     double* part = c.pow_part;
     for (int l = 0; l < A.nlev; ++l) {
       A.lv[l].part = part;

@@ -19,10 +19,11 @@ namespace ipmg {
 
 namespace {
 
-// Device memory of the context (Ctx::arena): small buffers share slabs.
+// Device memory of the context (Ctx::arena) for a buffer that has none yet: small
+// buffers share slabs.
 template <typename P>
 void dalloc(Ctx& c, P*& p, size_t bytes) {
-  p = (P*)c.arena.alloc(bytes);
+  c.arena.need(p, bytes);
 }
 
 // Safeguard of the Jacobi damping on every level except the coarsest:
@@ -104,7 +105,6 @@ void read_scalars(Ctx& c, const double* extra) {
 }
 
 static void ensure_z_buffers(Ctx& c) {
-  if (c.h64) return;
   const Dims& d = c.fine();
   const size_t m = (size_t)d.m, n1 = (size_t)d.nslots + 1;
   dalloc(c, c.h64, sizeof(double) * c.nd * m);
@@ -401,7 +401,6 @@ static void damping_all(Ctx& c, int op, int steps, double product) {
 }
 
 static void ensure_dense(Ctx& c) {
-  if (c.dA) return;
   const int64_t n = c.lev[0].d.nslots + 1;
   IPMG_REQUIRE(n <= DENSE_MAX_N, IPMG_E_INVALID, "coarsest level too large for the dense solve; use more levels");
   const int64_t np = dense_packed_size((int)n), nt = dense_tiles((int)n);
@@ -881,7 +880,7 @@ int pcg_noalloc(Ctx& c, int op, const double* b, double* u, double rtol, int max
 void oc_update(Ctx& c, const double* u, const double* x, double V, double xbar, double q, double lam_hi,
                double tau, const double* blend, double* x_new, ipmg_oc_info* info) {
   const Dims& d = c.fine();
-  if (!c.oc_t) dalloc(c, c.oc_t, sizeof(double) * (size_t)d.m);
+  dalloc(c, c.oc_t, sizeof(double) * (size_t)d.m);
   c.ops->oc_energy(c, u, x, q, c.oc_t);
   // trials of sequential bisection in exact arithmetic, plus two for rounding;
   // passes past the end are gated on the device
@@ -913,8 +912,8 @@ void oc_update(Ctx& c, const double* u, const double* x, double V, double xbar, 
 int simp_compliance(Ctx& c, const double* x, const double* f, double rmin, double p, double rtol, int maxit,
                     double* u, double* grad, ipmg_pcg_info* info) {
   const Dims& d = c.fine();
-  if (!c.simp_xt) dalloc(c, c.simp_xt, sizeof(double) * (size_t)d.m);
-  if (!c.simp_xp) dalloc(c, c.simp_xp, sizeof(double) * (size_t)d.m);
+  dalloc(c, c.simp_xt, sizeof(double) * (size_t)d.m);
+  dalloc(c, c.simp_xp, sizeof(double) * (size_t)d.m);
   c.ops->filter(c, rmin, x, c.simp_xt, 0);
   c.ops->simp_pow(c, c.simp_xt, p, c.simp_xp, nullptr);
   IPMG_HIP(hipGetLastError());
@@ -933,11 +932,10 @@ int simp_compliance(Ctx& c, const double* x, const double* f, double rmin, doubl
 
 // ------------------------------------------------------- SIMP interior point --
 static void ensure_simp_buffers(Ctx& c) {
-  if (c.simp_cf) return;
   const Dims& d = c.fine();
   const size_t m = (size_t)d.m;
-  if (!c.simp_xt) dalloc(c, c.simp_xt, sizeof(double) * m);
-  if (!c.simp_xp) dalloc(c, c.simp_xp, sizeof(double) * m);
+  dalloc(c, c.simp_xt, sizeof(double) * m);
+  dalloc(c, c.simp_xp, sizeof(double) * m);
   for (double** b : {&c.simp_cf, &c.simp_E, &c.simp_a, &c.simp_t, &c.simp_b1, &c.simp_b2, &c.simp_b3, &c.simp_bcoef,
                      &c.simp_rcoef})
     dalloc(c, *b, sizeof(double) * m);
