@@ -80,6 +80,9 @@ struct LamPend {
 
 // Passes of a level in node-stencil form (the kernels' StenMode).
 enum StenPass { SP_JACOBI2 = 0, SP_JACOBI = 1, SP_RESID = 2, SP_BETA = 3 };
+// Sizes of 2D levels where their passes change: from the first one on register-blocked
+// tiles, below the second one fused passes that stage the element matrices in LDS.
+constexpr int64_t TILED_MIN_NODES = (int64_t)1 << 17, STAGED_MAX_NODES = (int64_t)1 << 16;
 // Largest order of the coarsest solve inside the one-workgroup V-cycle (its threads).
 constexpr int TAIL_MAX_LD = 512;
 
@@ -212,11 +215,11 @@ struct Ctx {
   size_t tsz = 4;              // sizeof(T) of the V-cycle
   bool coarse_from_x = true;   // 2D K: first coarse level evaluated from the fine densities
   bool tiled2d = true;         // 2D level passes with register-blocked tiles
-  int64_t tiled_min_nodes = (int64_t)1 << 17;  // ... on levels with at least this many nodes
+  int64_t tiled_min_nodes = TILED_MIN_NODES;   // ... on levels with at least this many nodes
   int nj32 = 4, nj64 = 2, nj_dir = 4;          // nodes per thread of the tiled passes
   bool fused2d = true;         // 2D K coarse levels: two fused launches per level
   bool fused_staged = true;    // ... with the element matrices staged in LDS (FP32 stored levels
-  int64_t staged_max_nodes = (int64_t)1 << 16;  // below this size)
+  int64_t staged_max_nodes = STAGED_MAX_NODES;  // below this size)
   int cus = 256;               // compute units of the device
   bool mfma = true;            // first coarse level's fused passes on the matrix cores (FP32)
   bool lane_share = true;      // finest-level 2D passes of K on lane-shared tiles (neighbour columns by DPP)

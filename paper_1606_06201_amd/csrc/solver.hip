@@ -197,14 +197,14 @@ void ctx_init(Ctx& c, const ipmg_desc& d, hipStream_t st) {
   if (const char* e = std::getenv("IPMG_NJ64")) c.nj64 = std::atoi(e);
   if (const char* e = std::getenv("IPMG_NJ_DIR")) c.nj_dir = std::atoi(e);
   if (const char* e = std::getenv("IPMG_NO_TAIL")) c.tail_on = e[0] != '1';
-  // a path chosen for the coarse levels by one of these runs on all of them
-  for (const char* v : {"IPMG_STORED_COARSE", "IPMG_UNTILED", "IPMG_UNFUSED", "IPMG_UNSTAGED",
-                        "IPMG_STAGED_MAX_NODES", "IPMG_TILED_MIN_NODES", "IPMG_NO_MFMA", "IPMG_NO_FOLD_RESTRICT", "IPMG_NO_ELEM_FINE3",
-                        "IPMG_NO_ELEM_HV"})
-    if (std::getenv(v)) c.tail_on = c.sten2d = false;
   c.power_steps = POWER_STEPS;
   c.power_steps_z = POWER_STEPS_Z;
   if (const char* e = std::getenv("IPMG_TILED_MIN_NODES")) c.tiled_min_nodes = std::max<int64_t>(0, std::atoll(e));
+  // A path other than the default one chosen for the 2D coarse levels or for the finest
+  // 3D level runs on all levels that have it: no stencils in 2D, no one-workgroup V-cycle.
+  if (!c.coarse_from_x || !c.tiled2d || !c.fused2d || !c.fused_staged || !c.mfma || !c.fold_restrict || !c.elem_fine3 ||
+      !c.elem_hv || c.staged_max_nodes != STAGED_MAX_NODES || c.tiled_min_nodes != TILED_MIN_NODES)
+    c.tail_on = c.sten2d = false;
   c.ncoarse = (int)std::min<int64_t>(c.lev[0].d.nslots + 1, (int64_t)1 << 30);
 
   // reductions
