@@ -1966,7 +1966,8 @@ __global__ __launch_bounds__(BS) void k_dir_apply2d(Op op, Dims d, const TY* __r
   // (for q'y).  A neighbour outside the grid or clamped is read at the clamped node
   // (0, j) of its row, where y and p_old are zero, so no load sits under a branch
   // or feeds a select and all of them are in flight together.  (p_old is finite
-  // on the first iteration too: both direction buffers start zeroed.)
+  // on the first iteration too: both direction buffers start zeroed, and are zeroed
+  // again after a breakdown.)
   const double bf = first ? 0.0 : beta;
   TY yc[NJ][2];
   double w[NJ + 2][3][2], acc[NJ][2], dg[NJ][2];

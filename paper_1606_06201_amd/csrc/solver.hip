@@ -803,6 +803,12 @@ int pcg(Ctx& c, int op, const double* b, double* u, double rtol, int maxit, ipmg
     vset_tol(c.stream, c.red, rtol);
     pcg_restart_direction(c, op, n);
   }
+  // The next solve's first direction is -y + 0 p_old (2D tiles, finest 3D level, SIMP), so
+  // p_old has to be finite.  A p that is not makes p'q not finite either: a breakdown.
+  if (status == IPMG_E_BREAKDOWN) {
+    vfill(c.stream, c.pp, 0.0, n);
+    vfill(c.stream, c.pp2, 0.0, n);
+  }
   auto t1 = std::chrono::steady_clock::now();
   inf.iters = c.hflags[F_ITERS];
   inf.restarts = restarts;
