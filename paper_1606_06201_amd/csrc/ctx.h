@@ -252,7 +252,7 @@ struct Ctx {
   void* xT = nullptr;          // V-cycle copy (aliases x64 in FP64 mode)
   double* h64 = nullptr;       // Z rank-one factors h_e (ND * m)
   void* hT = nullptr;
-  void* hsbuf = nullptr;       // per-element h_e'v_e (m values, FP64 or FP32) for the 3D Z passes
+  void* hsbuf = nullptr;       // h_e'v_e per element (m values) for the 3D Z passes in gather form
   bool elem_hv = true;         // gather form of the 3D Z passes: form h_e'v_e per element first
   double* bZ64 = nullptr;      // border of Z on the finest grid (n_slots)
   double cZ = 0.0;             // corner of Z

@@ -1474,7 +1474,6 @@ struct OpsImpl : Ops {
       t.z = (T*)l.z;
       t.nslots = (int)l.d.nslots;
       t.ny1 = l.d.ny1;
-      t.nz1 = l.d.nz1;
       t.rx = 1.0f / (float)l.d.nx1;
       t.ry = 1.0f / (float)l.d.ny1;
       t.pad = (int)tail_pad(l.d);

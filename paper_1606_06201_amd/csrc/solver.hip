@@ -110,7 +110,7 @@ static void ensure_z_buffers(Ctx& c) {
   dalloc(c, c.h64, sizeof(double) * c.nd * m);
   if (c.fp32) dalloc(c, c.hT, sizeof(float) * c.nd * m);
   else c.hT = c.h64;
-  dalloc(c, c.hsbuf, sizeof(double) * m);   // h_e'v_e of the operator pass in flight
+  if (c.dim == 3 && !c.elem_fine3 && c.elem_hv) dalloc(c, c.hsbuf, sizeof(double) * m);
   dalloc(c, c.bZ64, sizeof(double) * n1);
   if (c.fp32) dalloc(c, c.lev[c.L - 1].bZ, sizeof(float) * n1);
   else c.lev[c.L - 1].bZ = c.bZ64;

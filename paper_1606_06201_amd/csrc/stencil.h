@@ -418,7 +418,7 @@ struct TailLevel {
   const T* border;      // (without a border: any readable slots, the lambda entry being 0)
   T* r;                 // right-hand side in memory (the top level's; all levels when split)
   T* z;                 // iterate in memory (the top level's result; all levels when split)
-  int nslots, ny1, nz1;
+  int nslots, ny1;
   float rx, ry;         // 1 / nx1, 1 / ny1
   int r_off, a_off, b_off, pad;   // LDS: r, the two iterates (level 0: the solution at a_off), zero pad after each
 };

@@ -27,8 +27,6 @@ template <typename TD, typename TS>
 void vconvert(hipStream_t st, const TS* src, TD* dst, int64_t n, const int* gate);
 void vset_tol(hipStream_t st, const Red& red, double rtol);
 void vset_rho(hipStream_t st, const Red& red, int sidx);
-template <typename T>
-void vnormalize(hipStream_t st, T* x, int64_t n, const Red& red, int sidx);
 void vfill(hipStream_t st, double* dst, double value, int64_t n);
 void vscale(hipStream_t st, double* v, double a, int64_t n);   // v *= a
 void vmul(hipStream_t st, const double* a, const double* b, double* out, int64_t n);   // out = a o b

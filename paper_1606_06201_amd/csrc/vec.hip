@@ -283,15 +283,6 @@ __global__ void k_fill_value(double* __restrict__ w, int n, double value) {
   if ((int)threadIdx.x < n) w[threadIdx.x] = value;
 }
 
-// x = x / sqrt(scal[sidx]) (power-iteration normalisation)
-template <typename T>
-__global__ __launch_bounds__(BS) void k_normalize(T* __restrict__ x, int64_t n, Red red, int sidx) {
-  const double s = red.scal[sidx];
-  const double inv = s > 0.0 ? 1.0 / sqrt(s) : 0.0;
-  for (int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x; t < n; t += (int64_t)gridDim.x * BS)
-    x[t] = T((double)x[t] * inv);
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------- launchers --
@@ -344,10 +335,6 @@ void vconvert(hipStream_t st, const TS* src, TD* dst, int64_t n, const int* gate
 }
 void vset_tol(hipStream_t st, const Red& red, double rtol) { k_set_tol<<<1, 64, 0, st>>>(red, rtol * rtol); }
 void vset_rho(hipStream_t st, const Red& red, int sidx) { k_set_rho<<<1, 64, 0, st>>>(red, sidx); }
-template <typename T>
-void vnormalize(hipStream_t st, T* x, int64_t n, const Red& red, int sidx) {
-  k_normalize<T><<<vgrid(n), BS, 0, st>>>(x, n, red, sidx);
-}
 void vfill(hipStream_t st, double* dst, double value, int64_t n) { k_fill<<<vgrid(n), BS, 0, st>>>(dst, value, n); }
 
 namespace {
@@ -669,7 +656,5 @@ template void vpcg_dir<double>(hipStream_t, double*, const double*, int64_t, con
 template void vconvert<float, double>(hipStream_t, const double*, float*, int64_t, const int*);
 template void vconvert<double, float>(hipStream_t, const float*, double*, int64_t, const int*);
 template void vconvert<double, double>(hipStream_t, const double*, double*, int64_t, const int*);
-template void vnormalize<float>(hipStream_t, float*, int64_t, const Red&, int);
-template void vnormalize<double>(hipStream_t, double*, int64_t, const Red&, int);
 
 }  // namespace ipmg
