@@ -199,8 +199,9 @@ int ipmg_apply_Z(ipmg_ctx* ctx, const double* v, double* y);
 int ipmg_pcg(ipmg_ctx* ctx, int op, const double* b, double* u, double rtol, int maxit,
              ipmg_pcg_info* info);
 
-/* For callers that cannot allocate device memory (code under HIP graph capture,
- * tight serving loops, harnesses that forbid hipMalloc): ipmg_pcg with its work
+/* For callers that cannot allocate device memory (tight serving loops, harnesses
+ * that forbid hipMalloc; not under graph capture, since the host reads the stop
+ * test): ipmg_pcg with its work
  * vectors (seven of n_slots + 1 doubles) and its reduction scratch in a static
  * device array of IPMG_NOALLOC_SCRATCH_BYTES that the library holds on each GPU
  * it runs on until the process ends, instead of the context's buffers.  The call

@@ -82,6 +82,10 @@ struct LamPend {
 enum StenPass { SP_JACOBI2 = 0, SP_JACOBI = 1, SP_RESID = 2, SP_BETA = 3 };
 // Sizes of 2D levels where their passes change: from the first one on register-blocked
 // tiles, below the second one fused passes that stage the element matrices in LDS.
+// First one: 20 PCG steps on K with it at 2^16 / 2^17 / 2^18 nodes, ms: FP32 512x256 2.11 / 2.10 /
+// 2.52, 704x352 2.38 / 2.37 / 2.79; FP64 3.04 / 3.03 / 3.61 and 3.43 / 3.37 / 4.05.  Tiles gain below
+// it too, from 2^16 on: 400x200 1.52 / 1.91 / 1.90 in FP32, 2.07 / 2.30 / 2.30 in FP64, 384x176 (68145
+// nodes) 1.91 / 2.24 / 2.25 in FP32.
 constexpr int64_t TILED_MIN_NODES = (int64_t)1 << 17, STAGED_MAX_NODES = (int64_t)1 << 16;
 // Largest order of the coarsest solve inside the one-workgroup V-cycle (its threads).
 constexpr int TAIL_MAX_LD = 512;

@@ -1371,11 +1371,23 @@ struct OpsImpl : Ops {
     return StenLevel<T>{(const T*)l.S, (const T*)l.dinv, (int)l.d.nnodes, l.d.nx1, l.d.nx1 * l.d.ny1};
   }
   // The one-workgroup tail takes the levels from the bottom up while their stencils
-  // stay below TAIL_BYTES each (one workgroup reads about 130 GB/s from L2: 640 KB
-  // is 5 us a pass, what a launch costs) and their vectors fit in its LDS; the
-  // finest level only below the register-blocked sizes.
+  // stay below TAIL_BYTES each and their vectors fit in its LDS; the finest level only
+  // below the register-blocked sizes.  What is past the first task of its waves one CU
+  // reads again in every pass, against a launch a pass.  20 PCG steps on K with the line
+  // at 160 / 320 / 640 KB, ms (medians of five processes):
+  //   FP32 48x24 (180 KB) 1.35 / 0.78 / 0.78, 64x32 (306 KB) 1.44 / 0.93 / 0.93, 72x36 (387 KB)
+  //   1.57 / 1.59 / 1.18, 88x44 (567 KB) 1.60 / 1.65 / 1.42; 3D 8x4x4 (243 KB) 1.50 / 0.82 / 0.82,
+  //   10x6x4 (425 KB) 1.52 / 1.54 / 1.08;
+  //   FP64 40x20 (252 KB) 1.26 / 0.96 / 0.96, 48x24 (360 KB) 1.29 / 1.33 / 1.13, 64x32 (612 KB) 1.73 /
+  //   1.44 / 1.60, 88x44 (its 44x22 level 306 KB) 1.59 / 1.76 / 1.75, 256x128 2.77 / 2.49 / 2.66.
+  // 320 KB is where FP64 with 64x32 and 256x128 elements is fastest; FP32 and 3D levels
+  // would gain up to 640 KB.
   static constexpr int64_t TAIL_BYTES = 320 * 1024;
-  // Largest 2D level on its stencil: at 2^18 nodes it is 38 MB in FP32, 75 MB in FP64.
+  // Largest 2D level on its stencil (38 MB in FP32, 75 MB in FP64); above, the element
+  // form reads less.  20 PCG steps on Z with the line at 2^17 / 2^18 / 2^19 nodes, ms: FP32
+  // 640x320 4.05 / 3.96 / 3.93, 704x352 4.15 / 4.31 / 4.30, 768x384 4.28 / 4.28 / 4.61, 960x480 4.73 /
+  // 4.73 / 5.46; FP64 640x320 4.35 / 4.81 / 4.82, 960x480 5.64 / 5.63 / 7.02.  FP64 would gain from
+  // a line at 2^17.
   static constexpr int64_t STEN_MAX_NODES = (int64_t)1 << 18;
   // LDS entries of a level's vectors: r, pad, a, pad, b, pad (level 0: r, z, pad); a
   // pad holds the neighbours that an index past either end of the grid can reach.
@@ -1402,15 +1414,16 @@ struct OpsImpl : Ops {
     if (lev < 1) return false;
     if (lev <= tail_level(c, op)) return true;
     if (DIM == 3) return lev < c.L - 1;
-    // 2D: the augmented system, and K in FP64, below the register-blocked sizes (one
-    // launch a sweep and two for the first pair; FP64 K before: 3.5 us passes that form
+    // 2D: the augmented system up to STEN_MAX_NODES, K in FP64 below the register-blocked
+    // sizes (one launch a sweep and two for the first pair; FP64 K before: 3.5 us passes that form
     // the element rows, 5.4 us on the first coarse level, fused pairs of 12.6 + 10.7 us)
     if (!c.sten2d) return false;
     return op == IPMG_OP_Z ? c.lev[lev].d.nnodes < STEN_MAX_NODES
                            : !c.fp32 && c.lev[lev].d.nnodes < c.tiled_min_nodes;
   }
   // Levels whose damping is estimated on the stencil, all in one launch per power step;
-  // for K in FP32 that is all their stencil is used for.
+  // for K in FP32 outside the tail that is all their stencil is used for (144 bytes a
+  // node, kept for the next set-up).
   bool pow_level(const Ctx& c, int lev, int op) const override {
     return sten_level(c, lev, op) ||
            (DIM == 2 && lev >= 1 && c.sten2d && c.lev[lev].d.nnodes < STEN_MAX_NODES);
@@ -1418,14 +1431,21 @@ struct OpsImpl : Ops {
   bool needs_elements(const Ctx& c, int lev, int op) const override {
     return DIM == 2 && lev >= 1 && lev < c.L - 1 && !sten_level(c, lev, op);
   }
-  // A^-1 of the coarsest level inside the tail: up to 200 KB (1.5 us of one
-  // workgroup's L2 reads; the two launches of the dense apply cost about 8 us).
+  // A^-1 of the coarsest level inside the tail: up to 200 KB, read by one CU in every
+  // cycle against three launches more (the dense apply's two and the tail's second).  20
+  // PCG steps on K in FP32 with the line at 100 / 200 / 400 KB, ms: 80x64 (coarsest 10x8,
+  // 198 KB) 1.68 / 1.52 / 1.56, 96x64 (12x8, 234 KB) 1.71 / 1.73 / 1.58, 128x64 (16x8, 382 KB) 1.85 /
+  // 1.85 / 1.86, 512x256 and 1024x512 (16x8) 2.13 / 2.16 / 2.22 and 3.02 / 3.03 / 3.10: the gain ends
+  // between 234 and 382 KB.
   bool tail_dense(const Ctx& c, int op) const {
     const int64_t n = c.lev[0].d.nslots + (op == IPMG_OP_Z ? 1 : 0), ld = (int64_t)dense_tiles((int)n) * DT;
     return n * ld * (int64_t)c.tsz <= 200 * 1024 && ld <= (c.fp32 ? TailNT<float>::value : TailNT<double>::value) / 2;
   }
   // Blocks whose partials every block of the next pass may add itself (16 KB);
-  // above, one block adds them in a launch of its own.
+  // above, one block adds them in a launch of its own.  20 PCG steps on Z with the line
+  // at 512 / 2048 / 8192, ms: FP32 256x128 (519 blocks) 2.46 / 2.29 / 2.28, 512x272 (2189) 3.74 / 3.53 /
+  // 3.42, 640x320 (3216) 4.39 / 3.96 / 3.94, 704x352 (3889) 4.40 / 4.28 / 4.31; FP64 640x320 4.95 / 4.82 /
+  // 4.93, 704x352 5.33 / 5.22 / 5.44.
   static constexpr unsigned LAM_FOLD_MAX = 2048;
 
   template <typename T>

@@ -3,9 +3,9 @@
 // of the damping estimate on it, and the V-cycle of all small levels in one
 // workgroup.
 //
-// Used for the stored 3D levels, for the levels of the augmented system in 2D below
-// the register-blocked sizes, and for every level of the one-workgroup tail.  A
-// pass over stored element matrices has to form element products and gather them
+// Used for the stored 3D levels, in 2D for the augmented system up to 2^18 nodes and
+// for K in FP64 below the register-blocked sizes, for the damping estimates of all 2D
+// levels up to 2^18 nodes, and for every level of the one-workgroup tail.  A pass over stored element matrices has to form element products and gather them
 // (3D: 300 matrix entries, 24 products written and read per element, two
 // launches) or to gather whole rows of 2^dim matrices per node (576 loads a node);
 // the assembled rows need 243 loads a node in 3D, 36 in 2D, each read once and
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(BS) void k_sten_power_fin(PowArgs<T> A, int steps, 
 // iterates of every level in LDS and runs a pass in 0.3 to 2 us behind a barrier.
 // What bounds a pass is the instruction latency of a wave on the small levels (few
 // waves have work), hence zero pads around the LDS vectors instead of index
-// clamping, and the 64 bytes a clock that one CU reads from L2 on the largest.
+// clamping, and what one CU reads again of the stencil on the largest.
 // The coarsest solve multiplies by the stored inverse; where that is too large for
 // one workgroup the tail runs as two launches (down, up) around the dense apply.
 // With the finest level in the tail the launch also ends the PCG step before it

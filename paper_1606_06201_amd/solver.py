@@ -257,6 +257,8 @@ class Solver:
         return x, u, log
 
     # ------------------------------------------------------------------ timing --
+    # elem3 and elem3_dir are accepted still, but no kernel records them: the finest 3D
+    # level's element products are part of the passes that the other classes name.
     KERNEL_CLASSES = {"fine_jacobi": 0, "dir_apply": 1, "fine_resid": 2, "pcg_update": 3, "sub_jacobi": 4,
                       "fine_jacobi0": 5, "fine_jacobi_beta": 6, "sub_down": 7, "sub_up": 8,
                       "fine_pjacobi": 11, "fine_jacobi2": 12, "elem3": 13,
